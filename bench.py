@@ -51,7 +51,7 @@ CSRC = os.path.join(ROOT, "paper_2608_00029_amd", "csrc")
 # Sources the attention kernels are compiled from (the loss head and the
 # memory-bound operators live in other files and do not change them).
 ATTN_SOURCES = ("attn_bf16.hip", "attn_fwd.hip", "attn_bwd.hip", "attn_device.h", "attn_sched.h", "attn_launch.h",
-                "bf16_stream.h")
+                "bf16_stream.h", "f32_stream.h")
 
 
 def kernel_source_digest(names=ATTN_SOURCES) -> str:

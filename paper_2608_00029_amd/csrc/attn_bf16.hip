@@ -940,8 +940,7 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-// Compute units of the current device (queried once per device).
-static int cu_count() {
+int cu_count() {
   static int cached[64] = {0};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;

@@ -1,17 +1,18 @@
-// Fused causal attention backward for gfx950: two kernels that recompute the
-// probabilities from the forward's log-sum-exp (section 4.2, backward
-// paragraph), so the S x S matrix never exists in memory, and that need no
-// atomics (every output element is owned by exactly one workgroup, and its
-// accumulation order is fixed, so results are bitwise reproducible).
+// Fused causal attention backward in float32 for gfx950: two kernels that
+// recompute the probabilities from the forward's log-sum-exp (section 4.2,
+// backward paragraph), so the S x S matrix never exists in memory, and that
+// need no atomics (every output element is owned by exactly one work group,
+// and its accumulation order is fixed, so results are bitwise reproducible).
+// bf16 calls go to attn_bf16.hip.
 //
-//  dq kernel   (reduces over keys; one workgroup per 128 queries, 32 per wave)
+//  dq kernel   (reduces over keys; one work group per 32*QG queries)
 //     D_i = sum_d dO_id O_id                      (float, written for the next kernel)
 //     per 32-key block:  S^T = K Q^T,  dP^T = V dO^T          (matrix cores)
 //                        P^T = exp2(S^T * scale*log2e - LSE_i*log2e)
 //                        dS^T = P^T * (dP^T - D_i)
 //                        dQ^T += K^T dS^T                      (matrix cores)
 //     dQ = scale * dQ^T^T
-//  dkdv kernel (reduces over queries; one workgroup per 128 keys, 32 per wave)
+//  dkdv kernel (reduces over queries; one work group per 32*KG keys)
 //     per 32-query block: S = Q K^T,  dP = dO V^T
 //                         P = exp2(S * scale*log2e - LSE*log2e), dS = P * (dP - D)
 //                         dV^T += dO^T P,  dK^T += Q^T dS
@@ -20,302 +21,245 @@
 // Both keep the score-like blocks in registers with one lane per query (dq)
 // or per key (dkdv), so LSE and D are per-lane scalars in the dq kernel, and
 // the probability block feeds the second contraction straight from registers.
-// The causal triangle is exploited on both sides: the dq key loop stops at the
-// diagonal (upper bound clamped), the dkdv query loop starts at it (lower bound
-// raised), and only blocks straddling the diagonal or the ragged sequence end
-// are masked.
+// The four waves of a work group split the reduced axis into interleaved parts
+// (f32_stream.h), added in part order through LDS.  The causal triangle is
+// exploited on both sides: the dq key loop stops at the diagonal (upper bound
+// clamped), the dkdv query loop starts at it (lower bound raised), and only
+// blocks straddling the diagonal or the ragged sequence end are masked.
 #include "attn_device.h"
 #include "attn_launch.h"
+#include "f32_stream.h"
 
 namespace cattn {
 
-template <typename T, int D, bool CAUSAL>
-__global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K,
-                                                          const T* __restrict__ V, const T* __restrict__ O,
-                                                          const T* __restrict__ dO, const float* __restrict__ LSE,
-                                                          T* __restrict__ dQ, float* __restrict__ Dvec, int S,
-                                                          int BH, int n_qtiles, float c, float scale, int H,
-                                                          int seq_major) {
-  typedef Mma<T> M;
-  constexpr int BQ = 128, BK = 64, NT = 256;
-  constexpr int KS_D = D / M::K, KS_32 = 32 / M::K, DT = D / 32;
-  constexpr int TILE = BK * D * (int)sizeof(T);
-  __shared__ __attribute__((aligned(16))) char smem[2 * 2 * TILE];  // [buffer][K, V]
+template <int D, bool CAUSAL, int QG, bool RAG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, 10)))
+void attn_bwd_dq_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+                            const float* __restrict__ O, const float* __restrict__ dO, const float* __restrict__ LSE,
+                            float* __restrict__ dQ, float* __restrict__ ws, int S, int BH, int n_qtiles, float c,
+                            float scale, int H, int seq_major, int band) {
+  typedef F32Geom<D> G;
+  constexpr int SPLIT = 4 / QG;
+  __shared__ f32x4 sm[f32_lds_units<D, QG, 2>()];
+  __shared__ float dpart[4][64];  // each wave's share of D = rowsum(dO * O)
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index: uniform, kept in an SGPR
+  const int qg = w % QG, part = w / QG;
   int bh, qt;
-  tile_of_block(blockIdx.x, BH, n_qtiles, CAUSAL, bh, qt);
+  tile_of_block_banded(blockIdx.x, BH, n_qtiles, CAUSAL, CAUSAL ? band : 0, bh, qt);
   const Rows rw = rows_of(bh, H, S, D, seq_major);
-  const int64_t base = rw.base;
-  const int rs = rw.rs;
-  const T* Kb = K + base;
-  const T* Vb = V + base;
+  const F32Mat<D, RAG> Qm{Q + rw.base, rw.rs, S, h, r}, Km{K + rw.base, rw.rs, S, h, r}, Vm{V + rw.base, rw.rs, S, h, r};
+  const F32Mat<D, RAG> Om{O + rw.base, rw.rs, S, h, r}, dOm{dO + rw.base, rw.rs, S, h, r};
 
-  const int q0 = qt * BQ, qw = q0 + 32 * w, my_q = qw + r;
-  typename M::frag qf[KS_D], dof[KS_D];
-  load_row_frags<T, D>(Q + base, my_q, S, h, rs, qf);
-  load_row_frags<T, D>(dO + base, my_q, S, h, rs, dof);
+  const int qw = (qt * QG + qg) * 32, my_q = qw + r;
+  const int n = qw >= S ? 0 : ((CAUSAL ? min(S, qw + 32) : S) + 31) / 32;  // key tiles (causal loop clamping)
 
-  // D = rowsum(dO * O) in float, from the O the forward produced.
-  float dpart = 0.f;
-  {
-    typename M::frag of[KS_D];
-    load_row_frags<T, D>(O + base, my_q, S, h, rs, of);
+  typename G::RowFrags kr;
+  if (part < n) Km.rows(part * 32, kr);
+  // Q and dO fragments of the query group into LDS, and D from the O the
+  // forward produced; each part loads every SPLIT-th chunk.
+  f32x4* qf = sm + qg * 2 * G::KJ * 64;
+  f32x4* dof = qf + G::KJ * 64;
+  float dsum = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < KS_D; ++ks) {
-      if constexpr (M::KL == 1) {
-        dpart = fmaf((float)dof[ks], (float)of[ks], dpart);
-      } else {
+  for (int i = 0; i < G::KJ / SPLIT; ++i) {
+    const int j = part + i * SPLIT;
+    qf[j * 64 + lane] = row_chunk(Qm.row_ptr(qw), j);
+    const f32x4 g = row_chunk(dOm.row_ptr(qw), j), o = row_chunk(Om.row_ptr(qw), j);
+    dof[j * 64 + lane] = g;
 #pragma unroll
-        for (int i = 0; i < M::KL; ++i) dpart = fmaf((float)dof[ks][i], (float)of[ks][i], dpart);
-      }
-    }
+    for (int e = 0; e < 4; ++e) dsum = fmaf(g[e], o[e], dsum);
   }
-  const float Dq = halves_sum(dpart);
+  dpart[w][lane] = dsum;
   const float lse = my_q < S ? LSE[(int64_t)bh * S + my_q] : 0.f;
+  __syncthreads();
+  dsum = dpart[qg][lane];
+#pragma unroll
+  for (int p = 1; p < SPLIT; ++p) dsum += dpart[qg + p * QG][lane];
+  const float Dq = halves_sum(dsum);
   const float lse2 = lse * kLog2e;
   const int Sp = ws_rows(S);
-  if (h == 0 && my_q < Sp) {  // workspace of this head: D row, then -LSE/scale row; padding entries are zero
-    float* wsh = Dvec + (int64_t)bh * 2 * Sp;
+  if (part == 0 && h == 0 && my_q < Sp) {  // workspace of this head: D row, then -LSE/scale row; padding is zero
+    float* wsh = ws + (int64_t)bh * 2 * Sp;
     wsh[my_q] = my_q < S ? Dq : 0.f;
     wsh[Sp + my_q] = my_q < S ? -lse / scale : 0.f;
   }
 
-  const int kend = CAUSAL ? min(S, q0 + BQ) : S;
-  const int n_kt = (kend + BK - 1) / BK;
-  f32x16 dqacc[DT];
+  f32x16 dqacc[G::DT];
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) dqacc[dt] = f32x16{};
+  for (int dt = 0; dt < G::DT; ++dt) dqacc[dt] = f32x16{};
 
-  TileStage<T, D, BK, NT> sk, sv;
-  sk.load(Kb, 0, S, tid, rs);
-  sv.load(Vb, 0, S, tid, rs);
-  sk.store(smem, tid);
-  sv.store(smem + TILE, tid);
-  __syncthreads();
-
-  for (int kt = 0; kt < n_kt; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < n_kt) {
-      sk.load(Kb, (kt + 1) * BK, S, tid, rs);
-      sv.load(Vb, (kt + 1) * BK, S, tid, rs);
-    }
-    const char* lk = smem + buf * 2 * TILE;
-    const char* lv = lk + TILE;
-#pragma unroll
-    for (int sb = 0; sb < BK / 32; ++sb) {
-      const int k0 = kt * BK + sb * 32;
-      if (k0 >= kend || (CAUSAL && k0 > qw + 31)) continue;  // wave-uniform skip
-      f32x16 s = f32x16{}, dp = f32x16{};
-#pragma unroll
-      for (int ks = 0; ks < KS_D; ++ks) {
-        s = M::run(read_row_frag<T, D>(lk, sb * 32 + r, ks, h), qf[ks], s);
-        dp = M::run(read_row_frag<T, D>(lv, sb * 32 + r, ks, h), dof[ks], dp);
-      }
-      if ((CAUSAL && k0 + 31 > qw) || k0 + 32 > S) {
-        // masked scores get the finite sentinel, whose exponential is exactly 0
-#pragma unroll
-        for (int a = 0; a < 16; ++a) {
-          const int key = k0 + acc_row(a, h);
-          if (key >= S || (CAUSAL && key > my_q)) s[a] = kMasked;
-        }
-      }
+  for (int t = part; t < n; t += SPLIT) {
+    const int k0 = t * 32;
+    // Each operand is loaded while the one before it is contracted.
+    typename G::RowFrags vr;
+    typename G::TransFrags kt;
+    const float* vp = Vm.row_ptr(k0);
+    f32x16 s = contract_rows<D, G::KJ>(kr, qf, lane, f32x16{}, [&](int j) { vr[j] = row_chunk(vp, j); });
+    f32x16 dp = contract_rows<D, 16>(vr, dof, lane, f32x16{}, [&](int a) { kt[a] = Km.trans_step(k0, a); });
+    if ((CAUSAL && k0 + 31 > qw) || (RAG && k0 + 32 > S)) {
+      // masked scores get the finite sentinel, whose exponential is exactly 0
 #pragma unroll
       for (int a = 0; a < 16; ++a) {
-        const float p = exp2_hw(fmaf(s[a], c, -lse2));
-        dp[a] = p * (dp[a] - Dq);  // dS^T
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS_32; ++ks) {
-        const typename M::frag db = M::pack(dp, ks);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-          dqacc[dt] = M::run(TransRead<T, D>::read(lk, sb * 32, ks, dt * 32, lane), db, dqacc[dt]);
+        const int key = k0 + acc_row(a, h);
+        if ((RAG && key >= S) || (CAUSAL && key > my_q)) s[a] = kMasked;
       }
     }
-    if (kt + 1 < n_kt) {
-      sk.store(smem + (buf ^ 1) * 2 * TILE, tid);
-      sv.store(smem + (buf ^ 1) * 2 * TILE + TILE, tid);
+#pragma unroll
+    for (int a = 0; a < 16; ++a) {
+      const float p = exp2_hw(fmaf(s[a], c, -lse2));
+      dp[a] = p * (dp[a] - Dq);  // dS^T
     }
-    __syncthreads();
+    const float* kn = Km.row_ptr(t + SPLIT < n ? k0 + 32 * SPLIT : k0);  // next tile (this one again after the last)
+    contract_tile<D, G::KJ>(kt, dp, dqacc, [&](int j) { kr[j] = row_chunk(kn, j); });
   }
 
-  if (my_q < S) {
-    T* row = dQ + base + (int64_t)my_q * rs;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        store4<T>(row + dt * 32 + 8 * g + 4 * h, dqacc[dt][4 * g] * scale, dqacc[dt][4 * g + 1] * scale,
-                  dqacc[dt][4 * g + 2] * scale, dqacc[dt][4 * g + 3] * scale);
-  }
+  sum_and_store<D, QG>(sm, w, h, lane, dqacc, dQ + rw.base + (int64_t)my_q * rw.rs, my_q < S, scale);
 }
 
-template <typename T, int D, bool CAUSAL>
-__global__ __launch_bounds__(256) void attn_bwd_dkdv_kernel(const T* __restrict__ Q, const T* __restrict__ K,
-                                                            const T* __restrict__ V, const T* __restrict__ dO,
-                                                            const float* __restrict__ LSE,
-                                                            const float* __restrict__ Dvec, T* __restrict__ dK,
-                                                            T* __restrict__ dV, int S, int BH, int n_ktiles,
-                                                            float c, float scale, int H, int seq_major) {
-  typedef Mma<T> M;
-  constexpr int BKV = 128, BQ = 64, NT = 256;
-  constexpr int KS_D = D / M::K, KS_32 = 32 / M::K, DT = D / 32;
-  constexpr int TILE = BQ * D * (int)sizeof(T);
-  constexpr int VEC = BQ * 4;                 // one float per query row
-  constexpr int BUF = 2 * TILE + 2 * VEC;     // Q, dO, LSE*log2e, D
-  __shared__ __attribute__((aligned(16))) char smem[2 * BUF];
+// At head dimension 128 the dK and dV accumulators and two operands in flight
+// take more than 256 registers: one wave per SIMD, whose 256 contractions per
+// block leave little else to overlap.
+template <int D, bool CAUSAL, int KG, bool RAG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1, 10)))
+void attn_bwd_dkdv_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+                              const float* __restrict__ dO, const float* __restrict__ LSE,
+                              const float* __restrict__ ws, float* __restrict__ dK, float* __restrict__ dV, int S,
+                              int BH, int n_ktiles, float c, float scale, int H, int seq_major, int band) {
+  typedef F32Geom<D> G;
+  constexpr int SPLIT = 4 / KG;
+  __shared__ f32x4 sm[f32_lds_units<D, KG, 2>()];
+  __shared__ __attribute__((aligned(16))) float aux[4][2][32];  // each wave's tile: LSE, D
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index: uniform, kept in an SGPR
+  const int kg = w % KG, part = w / KG;
   int bh, kt;
-  tile_of_block(blockIdx.x, BH, n_ktiles, false, bh, kt);
+  tile_of_block_banded(blockIdx.x, BH, n_ktiles, false, CAUSAL ? band : 0, bh, kt);
   const Rows rw = rows_of(bh, H, S, D, seq_major);
-  const int64_t base = rw.base;
-  const int rs = rw.rs;
-  const T* Qb = Q + base;
-  const T* dOb = dO + base;
+  const F32Mat<D, RAG> Qm{Q + rw.base, rw.rs, S, h, r}, dOm{dO + rw.base, rw.rs, S, h, r};
+  const F32Mat<D, RAG> Km{K + rw.base, rw.rs, S, h, r}, Vm{V + rw.base, rw.rs, S, h, r};
   const float* Lb = LSE + (int64_t)bh * S;
-  const float* Db = Dvec + (int64_t)bh * 2 * ws_rows(S);
+  const float* Db = ws + (int64_t)bh * 2 * ws_rows(S);
 
-  const int k0 = kt * BKV, kw = k0 + 32 * w, my_k = kw + r;
-  typename M::frag kf[KS_D], vf[KS_D];
-  load_row_frags<T, D>(K + base, my_k, S, h, rs, kf);
-  load_row_frags<T, D>(V + base, my_k, S, h, rs, vf);
+  const int kw = (kt * KG + kg) * 32, my_k = kw + r;
+  const int nt = (S + 31) / 32;  // query tiles of the sequence
+  // causal: the query loop starts at the diagonal; a group past the end has none
+  const int t0 = kw >= S ? nt : (CAUSAL ? kw / 32 : 0) + part;
 
-  const int qstart = CAUSAL ? k0 : 0;  // causal: the query loop starts at the diagonal
-  const int qt0 = qstart / BQ;
-  const int n_qt = (S + BQ - 1) / BQ;
-  f32x16 dkacc[DT], dvacc[DT];
+  typename G::RowFrags qr;
+  float lse_row = 0.f, d_row = 0.f;
+  if (t0 < nt) {
+    Qm.rows(t0 * 32, qr);
+    lse_row = Lb[min(t0 * 32 + r, S - 1)];
+    d_row = Db[t0 * 32 + r];  // rows are padded to 32 entries
+  }
+  f32x4* kf = sm + kg * 2 * G::KJ * 64;
+  f32x4* vf = kf + G::KJ * 64;
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) {
+  for (int i = 0; i < G::KJ / SPLIT; ++i) {
+    const int j = part + i * SPLIT;
+    kf[j * 64 + lane] = row_chunk(Km.row_ptr(kw), j);
+    vf[j * 64 + lane] = row_chunk(Vm.row_ptr(kw), j);
+  }
+  __syncthreads();
+
+  f32x16 dkacc[G::DT], dvacc[G::DT];
+#pragma unroll
+  for (int dt = 0; dt < G::DT; ++dt) {
     dkacc[dt] = f32x16{};
     dvacc[dt] = f32x16{};
   }
 
-  TileStage<T, D, BQ, NT> sq, sdo;
-  float vec = 0.f;  // threads 0..63 stage LSE*log2e, threads 64..127 stage D
-  auto load_tile = [&](int qt) {
-    sq.load(Qb, qt * BQ, S, tid, rs);
-    sdo.load(dOb, qt * BQ, S, tid, rs);
-    const int row = qt * BQ + (tid & 63);
-    vec = 0.f;
-    if (tid < 64) {
-      if (row < S) vec = Lb[row] * kLog2e;
-    } else if (tid < 128) {
-      if (row < S) vec = Db[row];
-    }
-  };
-  auto store_tile = [&](char* b) {
-    sq.store(b, tid);
-    sdo.store(b + TILE, tid);
-    if (tid < 128) ((float*)(b + 2 * TILE))[tid] = vec;  // [0,64): LSE*log2e, [64,128): D
-  };
-
-  if (qt0 < n_qt) {
-    load_tile(qt0);
-    store_tile(smem);
-  }
-  __syncthreads();
-
-  for (int qt = qt0; qt < n_qt; ++qt) {
-    const int buf = (qt - qt0) & 1;
-    if (qt + 1 < n_qt) load_tile(qt + 1);
-    const char* lq = smem + buf * BUF;
-    const char* ldo = lq + TILE;
-    const float* llse = (const float*)(lq + 2 * TILE);
-    const float* ld = llse + BQ;
+  for (int t = t0; t < nt; t += SPLIT) {
+    const int q0 = t * 32;
+    // Each operand is loaded while the one before it is contracted.
+    typename G::RowFrags dor;
+    typename G::TransFrags dot, qtr;
+    const float* dop = dOm.row_ptr(q0);
+    // this tile's LSE and D, one row per lane, to the lanes in accumulator order
+    aux[w][0][r] = lse_row;
+    aux[w][1][r] = d_row;
+    f32x16 s = contract_rows<D, G::KJ>(qr, kf, lane, f32x16{}, [&](int j) { dor[j] = row_chunk(dop, j); });
+    f32x16 dp = contract_rows<D, 16>(dor, vf, lane, f32x16{}, [&](int a) { dot[a] = dOm.trans_step(q0, a); });
+    // s[a], dp[a]: query q0 + acc_row(a, h), key my_k
+    if ((CAUSAL && q0 < kw + 31) || (RAG && q0 + 32 > S)) {
+      // masked scores get the finite sentinel, whose exponential is exactly 0
 #pragma unroll
-    for (int sb = 0; sb < BQ / 32; ++sb) {
-      const int q0 = qt * BQ + sb * 32;
-      if (q0 >= S || (CAUSAL && q0 + 31 < kw)) continue;  // wave-uniform skip
-      f32x16 s = f32x16{}, dp = f32x16{};
-#pragma unroll
-      for (int ks = 0; ks < KS_D; ++ks) {
-        s = M::run(read_row_frag<T, D>(lq, sb * 32 + r, ks, h), kf[ks], s);
-        dp = M::run(read_row_frag<T, D>(ldo, sb * 32 + r, ks, h), vf[ks], dp);
-      }
-      // s[a], dp[a]: query q0 + acc_row(a, h), key my_k
-      if ((CAUSAL && q0 < kw + 31) || q0 + 32 > S) {
-        // masked scores get the finite sentinel, whose exponential is exactly 0
-#pragma unroll
-        for (int a = 0; a < 16; ++a) {
-          const int qry = q0 + acc_row(a, h);
-          if (qry >= S || (CAUSAL && my_k > qry)) s[a] = kMasked;
-        }
-      }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 l4 = *(const f32x4*)(llse + sb * 32 + 8 * g + 4 * h);
-        const f32x4 d4 = *(const f32x4*)(ld + sb * 32 + 8 * g + 4 * h);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int a = 4 * g + j;
-          const float p = exp2_hw(fmaf(s[a], c, -l4[j]));
-          s[a] = p;
-          dp[a] = p * (dp[a] - d4[j]);  // dS
-        }
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS_32; ++ks) {
-        const typename M::frag pb = M::pack(s, ks);
-        const typename M::frag db = M::pack(dp, ks);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          dvacc[dt] = M::run(TransRead<T, D>::read(ldo, sb * 32, ks, dt * 32, lane), pb, dvacc[dt]);
-          dkacc[dt] = M::run(TransRead<T, D>::read(lq, sb * 32, ks, dt * 32, lane), db, dkacc[dt]);
-        }
+      for (int a = 0; a < 16; ++a) {
+        const int qry = q0 + acc_row(a, h);
+        if ((RAG && qry >= S) || (CAUSAL && my_k > qry)) s[a] = kMasked;
       }
     }
-    if (qt + 1 < n_qt) store_tile(smem + (buf ^ 1) * BUF);
-    __syncthreads();
+    const int qn = t + SPLIT < nt ? q0 + 32 * SPLIT : q0;  // next tile (this one again after the last)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 l4 = *(const f32x4*)&aux[w][0][8 * g + 4 * h], d4 = *(const f32x4*)&aux[w][1][8 * g + 4 * h];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int a = 4 * g + e;
+        const float p = exp2_hw(fmaf(s[a], c, -l4[e] * kLog2e));
+        s[a] = p;
+        dp[a] = p * (dp[a] - d4[e]);  // dS
+      }
+    }
+    contract_tile<D, 16>(dot, s, dvacc, [&](int a) { qtr[a] = Qm.trans_step(q0, a); });
+    const float* qp = Qm.row_ptr(qn);
+    lse_row = Lb[min(qn + r, S - 1)];
+    d_row = Db[qn + r];  // rows are padded to 32 entries
+    contract_tile<D, G::KJ>(qtr, dp, dkacc, [&](int j) { qr[j] = row_chunk(qp, j); });
   }
 
-  if (my_k < S) {
-    T* krow = dK + base + (int64_t)my_k * rs;
-    T* vrow = dV + base + (int64_t)my_k * rs;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = dt * 32 + 8 * g + 4 * h;
-        store4<T>(krow + col, dkacc[dt][4 * g] * scale, dkacc[dt][4 * g + 1] * scale, dkacc[dt][4 * g + 2] * scale,
-                  dkacc[dt][4 * g + 3] * scale);
-        store4<T>(vrow + col, dvacc[dt][4 * g], dvacc[dt][4 * g + 1], dvacc[dt][4 * g + 2], dvacc[dt][4 * g + 3]);
-      }
-  }
+  // dV, then dK, through the same LDS area
+  const int64_t row = rw.base + (int64_t)my_k * rw.rs;
+  sum_and_store<D, KG>(sm, w, h, lane, dvacc, dV + row, my_k < S, 1.f);
+  sum_and_store<D, KG>(sm, w, h, lane, dkacc, dK + row, my_k < S, scale);
 }
 
-template <typename T, int D, bool CAUSAL>
+template <int D, bool CAUSAL, int G, bool RAG>
 static hipError_t launch_bwd_t(const BwdArgs& a, int phase, hipStream_t st) {
   const float c = a.scale * kLog2e;
+  const int n_tiles = (a.S + 32 * G - 1) / (32 * G);
+  const int64_t n = (int64_t)a.BH * n_tiles;
+  const dim3 grid((unsigned)n);
+  // dealt in alternating directions when every work group is resident from the
+  // start (dK/dV at D = 64: when at most a third of them start later, which
+  // measured 71 us against 75 at B2 H12 S1024)
+  const int cus = cu_count(), dq_band = n <= (D == 64 ? 3 : 2) * cus ? cus : 0;
+  const int dkdv_band = n <= (D == 64 ? 3 : 1) * cus ? cus : 0;
   if (phase != 2) {
-    const int n_qtiles = (a.S + 127) / 128;
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D, CAUSAL>), dim3((unsigned)((int64_t)a.BH * n_qtiles)), dim3(256),
-                       0, st, (const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.o, (const T*)a.dout, a.lse,
-                       (T*)a.dq, a.ws, a.S, a.BH, n_qtiles, c, a.scale, a.H, (int)a.seq_major);
+    hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<D, CAUSAL, G, RAG>), grid, dim3(256), 0, st, (const float*)a.q,
+                       (const float*)a.k, (const float*)a.v, (const float*)a.o, (const float*)a.dout, a.lse,
+                       (float*)a.dq, a.ws, a.S, a.BH, n_tiles, c, a.scale, a.H, (int)a.seq_major, dq_band);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || phase == 1) return e;
   }
-  const int n_ktiles = (a.S + 127) / 128;
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<T, D, CAUSAL>), dim3((unsigned)((int64_t)a.BH * n_ktiles)), dim3(256),
-                     0, st, (const T*)a.q, (const T*)a.k, (const T*)a.v, (const T*)a.dout, a.lse, a.ws,
-                     (T*)a.dk, (T*)a.dv, a.S, a.BH, n_ktiles, c, a.scale, a.H, (int)a.seq_major);
+  hipLaunchKernelGGL((attn_bwd_dkdv_f32_kernel<D, CAUSAL, G, RAG>), grid, dim3(256), 0, st, (const float*)a.q,
+                     (const float*)a.k, (const float*)a.v, (const float*)a.dout, a.lse, (const float*)a.ws,
+                     (float*)a.dk, (float*)a.dv, a.S, a.BH, n_tiles, c, a.scale, a.H, (int)a.seq_major, dkdv_band);
   return hipGetLastError();
 }
 
-template <typename T, int D>
+template <int D, bool CAUSAL, bool RAG>
+static hipError_t launch_bwd_g(const BwdArgs& a, int phase, hipStream_t st) {
+  return f32_groups(a.BH, a.S, cu_count()) == 2 ? launch_bwd_t<D, CAUSAL, 2, RAG>(a, phase, st)
+                                                : launch_bwd_t<D, CAUSAL, 1, RAG>(a, phase, st);
+}
+
+template <int D>
 static hipError_t launch_bwd_d(const BwdArgs& a, int phase, hipStream_t st) {
-  return a.causal ? launch_bwd_t<T, D, true>(a, phase, st) : launch_bwd_t<T, D, false>(a, phase, st);
+  if (f32_ragged(a.S, a.seq_major ? (int64_t)a.H * D : D))
+    return a.causal ? launch_bwd_g<D, true, true>(a, phase, st) : launch_bwd_g<D, false, true>(a, phase, st);
+  return a.causal ? launch_bwd_g<D, true, false>(a, phase, st) : launch_bwd_g<D, false, false>(a, phase, st);
 }
 
 hipError_t launch_bwd(const BwdArgs& a, int phase, hipStream_t st) {
   if (a.bf16) return launch_bwd_bf16(a, phase, st);
-  return a.D == 64 ? launch_bwd_d<float, 64>(a, phase, st) : launch_bwd_d<float, 128>(a, phase, st);
+  return a.D == 64 ? launch_bwd_d<64>(a, phase, st) : launch_bwd_d<128>(a, phase, st);
 }
 
-// upper bound over the backward launch shapes (the smallest key tile is 64 rows)
-int64_t bwd_grid_blocks(int BH, int S) { return (int64_t)BH * ((S + 63) / 64); }
+// upper bound over the backward launch shapes (the smallest tile is 32 rows)
+int64_t bwd_grid_blocks(int BH, int S) { return (int64_t)BH * ((S + 31) / 32); }
 
 }  // namespace cattn

@@ -1,10 +1,10 @@
 // Device-side building blocks shared by the forward and backward attention
 // kernels for gfx950 (CDNA4): matrix-core operand fragments, the swizzled LDS
-// tile layout, global->LDS tile staging and cross-half wave reductions.
+// tile layout and cross-half wave reductions.
 //
 // Matrix-core shape.  Every contraction is issued as 32x32 output blocks:
 //   bf16: v_mfma_f32_32x32x16_bf16  (A 32x16, B 16x32, C 32x32 float)
-//   f32 : v_mfma_f32_32x32x2_f32    (A 32x2,  B 2x32,  C 32x32 float)
+//   f32 : v_mfma_f32_32x32x2_f32    (A 32x2,  B 2x32,  C 32x32 float; f32_stream.h)
 // A lane L = 32*h + r (h = half of the wave, r = L % 32) supplies row r of A
 // and column r of B, each holding KL consecutive contraction elements starting
 // at h*KL (KL = 8 for bf16, 1 for f32).  It receives the C entries
@@ -63,16 +63,6 @@ template <> struct Mma<__bf16> {
     for (int i = 0; i < 8; ++i) f[i] = (__bf16)acc[8 * s + i];
     return f;
   }
-};
-
-template <> struct Mma<float> {
-  static constexpr int K = 2;
-  static constexpr int KL = 1;
-  typedef float frag;
-  static __device__ __forceinline__ f32x16 run(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ frag pack(const f32x16& acc, int s) { return acc[s]; }
 };
 
 // Row (within a 32-row block) that accumulator index a of half h refers to.
@@ -135,47 +125,6 @@ template <int D> struct TransRead<__bf16, D> {
   }
 };
 
-template <int D> struct TransRead<float, D> {
-  static __device__ __forceinline__ float read(const char* lds, int rb, int s, int n0, int lane) {
-    const int h = lane >> 5;
-    return *(const float*)(lds + Tile<float, D>::off(rb + acc_row(s, h), n0 + (lane & 31)));
-  }
-};
-
-// ---------------------------------------------------------------------------
-// Global -> registers -> LDS staging of an R x D tile (rows >= nrows are zero).
-// Consecutive threads take consecutive 16-byte chunks of a row, so each row is
-// one fully coalesced 128/256-byte segment.
-// ---------------------------------------------------------------------------
-template <typename T, int D, int R, int NT> struct TileStage {
-  static constexpr int kChunksPerRow = Tile<T, D>::kChunks;
-  static constexpr int kPerThread = R * kChunksPerRow / NT;
-  static_assert(R * kChunksPerRow % NT == 0, "tile must split evenly over the threads");
-  u32x4 reg[kPerThread];
-
-  // rows of g are rs elements apart
-  __device__ __forceinline__ void load(const T* g, int row0, int nrows, int tid, int rs) {
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      const int c = tid + i * NT;
-      const int row = c / kChunksPerRow, ch = c % kChunksPerRow;
-      if (row0 + row < nrows) {
-        reg[i] = *(const u32x4*)((const char*)g + ((int64_t)(row0 + row) * rs) * (int64_t)sizeof(T) + ch * 16);
-      } else {
-        reg[i] = u32x4{0u, 0u, 0u, 0u};
-      }
-    }
-  }
-  __device__ __forceinline__ void store(char* lds, int tid) const {
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      const int c = tid + i * NT;
-      const int row = c / kChunksPerRow, ch = c % kChunksPerRow;
-      *(u32x4*)(lds + row * Tile<T, D>::kRowBytes + ((ch ^ swz(row)) << 4)) = reg[i];
-    }
-  }
-};
-
 // ---------------------------------------------------------------------------
 // Cross-half reductions: combine lane r with lane r + 32 (v_permlane32_swap
 // exchanges the upper half of its first operand with the lower half of its
@@ -207,9 +156,6 @@ __device__ __forceinline__ float wave_sum(float x) {
 
 // Store 4 consecutive row elements (one accumulator run) converted to T.
 template <typename T> __device__ __forceinline__ void store4(T* dst, float a, float b, float c, float d);
-template <> __device__ __forceinline__ void store4<float>(float* dst, float a, float b, float c, float d) {
-  *(f32x4*)dst = f32x4{a, b, c, d};
-}
 template <> __device__ __forceinline__ void store4<__bf16>(__bf16* dst, float a, float b, float c, float d) {
   bf16x4 v;
   v[0] = (__bf16)a; v[1] = (__bf16)b; v[2] = (__bf16)c; v[3] = (__bf16)d;

@@ -49,6 +49,8 @@ hipError_t launch_bwd(const BwdArgs& a, int phase, hipStream_t st);
 // bf16 kernels (attn_bf16.hip); launch_fwd / launch_bwd route bf16 calls here
 hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t st);
 hipError_t launch_bwd_bf16(const BwdArgs& a, int phase, hipStream_t st);
+// compute units of the current device (queried once per device)
+int cu_count();
 int64_t fwd_grid_blocks(int BH, int S);
 int64_t bwd_grid_blocks(int BH, int S);
 

@@ -35,7 +35,10 @@ constexpr int ring_in_flight_full(int split, int ahead, int need) { return (ahea
 // GPU in rounds of `band` (one per compute unit): group b shares its compute
 // unit with groups b +- band, b +- 2 band, ...  Every other round walks the
 // ranks backwards, so that a compute unit that receives one of the heaviest
-// items in one round receives one of the lightest of the next.  The walk is
+// items in one round receives one of the lightest of the next; the last round,
+// which may be short and falls on the first units, always walks forwards, and
+// the rounds before it alternate up to it, so that the units it reaches are
+// those with the least before it.  The walk is
 // backwards in steps of kXcdGroup, keeping each rank's position within its
 // group of kXcdGroup: work groups are dealt to the GPU's kXcdGroup chiplets
 // (each with its own L2) round-robin by index, and a rank keeps the chiplet of
@@ -45,8 +48,8 @@ constexpr int ring_in_flight_full(int split, int ahead, int need) { return (ahea
 constexpr int kXcdGroup = 8;
 constexpr int banded_rank(int bid, int n, int band) {
   if (band <= 0) return bid;
-  const int r = bid / band, p = bid % band;
-  if ((r & 1) == 0) return bid;
+  const int r = bid / band, p = bid % band, last = (n - 1) / band;
+  if (((last - r) & 1) == 0) return bid;
   const int size = n - r * band < band ? n - r * band : band;
   if (size % kXcdGroup != 0 || band % kXcdGroup != 0) return r * band + size - 1 - p;
   return r * band + (size / kXcdGroup - 1 - p / kXcdGroup) * kXcdGroup + p % kXcdGroup;
