@@ -8,25 +8,39 @@
 //
 // Kernel 1 (projection + statistics).  A persistent grid of one work group
 // per compute unit; each walks its chiplet's 256 x 256 output tiles (256
-// vocabulary rows x 256 tokens of Z) and streams K in chunks of 64 through two
-// LDS slots (W and X rows of a chunk, 64 KB each): the copy of chunk c + 1 --
-// or of the next tile's first chunk -- runs while chunk c computes, so the
-// next tile's first copy also overlaps this tile's epilogue.  Each of the
-// eight waves computes a 128 x 64 block as 4 x 2 transposed 32 x 32
-// matrix-core blocks, Z^T = W X^T, so that every lane holds one token and 16
-// vocabulary entries of each block: the row statistics are then in-lane over
-// 32 entries plus one swap between the wave halves, exactly as the attention
-// kernels' row softmax.  A partial covers 64 vocabulary entries: partials are
-// [M, N/64] pairs (maximum, sum of exp(z - maximum)).  Logits are written as
-// float [M, N].  A 256 x 256 tile does 128 FLOPs per byte it brings into LDS,
-// twice what a 128 x 128 tile does, which is what keeps the chiplets' L2
-// bandwidth from capping the matrix cores.
+// vocabulary rows x 256 tokens of Z).  What bounds it, at 8192 x 50304 x 768:
+// the contractions need 0.30 ms of matrix-core time at the ~2 GHz this load
+// holds, the 1.65 GB of logits about 0.3 ms of HBM, and every tile brings
+// 0.8 MB through L2 (128 FLOPs per byte).  So:
+//  * K streams in chunks of 32 through four LDS slots (W and X rows of a
+//    chunk, 32 KB), copied three chunks ahead, across tiles: the barrier of a
+//    chunk waits for the next one, so that operand fragments are read one
+//    k-step ahead also across chunks.  An iteration is two chunks and has no
+//    taken branch, and the copies' instructions sit between contractions: the
+//    eight waves meet at every barrier, so whatever precedes the first
+//    contraction after it idles all matrix cores.  Measured without copies and
+//    stores: 0.57 us per chunk of 0.50 us of contractions.
+//  * Each of the eight waves computes 64 tokens x 128 vocabulary entries as
+//    2 x 4 matrix-core blocks whose four vocabulary blocks interleave (block a
+//    holds entries 4 r + a), so that a lane's four accumulators of one token
+//    are four consecutive logits and a store writes 512 consecutive bytes of
+//    two token rows.  (The transposed blocks used before, one token per lane,
+//    left each lane its own 16-byte piece of a line.)
+//  * The stores are non-temporal, and the waits for copies leave them in
+//    flight for two chunks of the next tile.
+//  * A partial statistic covers 64 vocabulary entries, 16 lanes of four: the
+//    row maximum takes four lane rotations per token, the sums are scattered
+//    over the lanes, halving the values per exchange.
+// Whole call, transposed blocks with chunks of 64 in two slots / this: 8192 x
+// 50304 x 768 916 / 754 us, 1024 x 50304 x 1600 221 / 201, 128 x 18432 x 1408
+// 35 / 32, 1152 x 11264 x 384 30 / 27.
 //
-// Tiles are dealt to the GPU's chiplets by vocabulary tile (modulo 8); a
-// chiplet walks its vocabulary tiles eight at a time with the token tiles
-// inside (lmhead_sched.h), so the W and X rows in flight on it fit its L2.
-// A ragged last tile (N or M not a multiple of 256; both are multiples of
-// 128) leaves the waves past the end idle and skips their copies.
+// Partials are [M, N/64] pairs (maximum, sum of exp(z - maximum)).  Logits are
+// written as float [M, N].  Tiles are dealt to the GPU's chiplets by vocabulary
+// tile (modulo 8); a chiplet walks its vocabulary tiles eight at a time with
+// the token tiles inside (lmhead_sched.h), so the W and X rows in flight on it
+// fit its L2.  A ragged last tile (N or M not a multiple of 256; both are
+// multiples of 128) leaves the waves past the end idle.
 //
 // Kernel 2 (merge): one wave per token row combines the row's N/64 partials
 // with the rescale-by-maximum-difference rule (the merge is not the fold),
@@ -43,14 +57,76 @@
 
 namespace cattn {
 
+// One 16-byte HBM -> LDS copy per lane, from a per-lane 64-bit address (see
+// dma16 for the rest).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void dma16_v(const void* src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+// LDS image of a chunk: 32-row blocks of 64-byte rows, four 16-byte pieces
+// each; the piece at logical position q of row r sits at q ^ lmh_swz(r).  The
+// 16-byte reads of 16 consecutive rows, or of 8 rows by both wave halves, then
+// touch every bank once.
+__device__ __forceinline__ int lmh_swz(int row) { return ((row & 4) >> 1) | ((row & 8) >> 3); }
+
+// Maximum of each of four values over the 16 lanes of a row; every lane gets
+// it.  One instruction per value and step: the four chains are interleaved so
+// that a value is read by its lane rotation three instructions after it was
+// written (two wait states are required; the s_nop covers the first step).
+__device__ __forceinline__ void row16_max4(float& a, float& b, float& c, float& d) {
+#define CATTN_MAX_STEP(n)                                                        \
+  "v_max_f32_dpp %0, %0, %0 row_ror:" #n " row_mask:0xf bank_mask:0xf\n\t"       \
+  "v_max_f32_dpp %1, %1, %1 row_ror:" #n " row_mask:0xf bank_mask:0xf\n\t"       \
+  "v_max_f32_dpp %2, %2, %2 row_ror:" #n " row_mask:0xf bank_mask:0xf\n\t"       \
+  "v_max_f32_dpp %3, %3, %3 row_ror:" #n " row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t" CATTN_MAX_STEP(8) CATTN_MAX_STEP(4) CATTN_MAX_STEP(2) CATTN_MAX_STEP(1) "s_nop 0"
+      : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+#undef CATTN_MAX_STEP
+}
+template <int CTRL> __device__ __forceinline__ float row_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+// hi if bit, else lo (by value: a choice between array elements would make the
+// arrays addressable and so move them to memory)
+__device__ __forceinline__ float pick(bool bit, float lo, float hi) { return bit ? hi : lo; }
+// Lane j of each 16-lane row gets the sum of v[j] over the row's lanes: halves
+// the values in each of four exchanges (lane j with j ^ 15, j ^ 7, j ^ 2,
+// j ^ 1) instead of summing all 16 in every lane.
+__device__ __forceinline__ float row16_sum_scatter(const float (&v)[16], int j) {
+  const bool b3 = j & 8, b2 = j & 4, b1 = j & 2, b0 = j & 1;
+  float p[8], q[4], u[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) p[i] = pick(b3, v[i], v[i + 8]) + row_move<0x140>(pick(b3, v[i + 8], v[i]));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) q[i] = pick(b2, p[i], p[i + 4]) + row_move<0x141>(pick(b2, p[i + 4], p[i]));
+#pragma unroll
+  for (int i = 0; i < 2; ++i) u[i] = pick(b1, q[i], q[i + 2]) + row_move<0x4E>(pick(b1, q[i + 2], q[i]));
+  return pick(b0, u[0], u[1]) + row_move<0xB1>(pick(b0, u[1], u[0]));
+}
+// v[j]
+__device__ __forceinline__ float select16(const float (&v)[16], int j) {
+  const bool b3 = j & 8, b2 = j & 4, b1 = j & 2, b0 = j & 1;
+  float p[8], q[4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) p[i] = pick(b3, v[i], v[i + 8]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) q[i] = pick(b2, p[i], p[i + 4]);
+  return pick(b0, pick(b1, q[0], q[2]), pick(b1, q[1], q[3]));
+}
+
 __global__ __launch_bounds__(512) void lmhead_logits_stats_kernel(const bf16* __restrict__ X,
                                                                   const bf16* __restrict__ W,
                                                                   float* __restrict__ Z, float* __restrict__ part,
                                                                   int M, int N, int K, int per_xcd) {
-  constexpr int TILE = 32 * kLmhKC * 2;  // one 32-row block of a chunk: 4 KB
-  constexpr int SLOT = 16 * TILE;        // W: 8 blocks (256 rows), X: 8 blocks (256 rows)
-  constexpr int KS = kLmhKC / 16;
-  __shared__ __attribute__((aligned(16))) char smem[2 * SLOT];
+  constexpr int BLK = 32 * kLmhKC * 2;   // one 32-row block of a chunk: 2 KB
+  constexpr int SLOT = 16 * BLK;         // W: 8 blocks (256 rows), X: 8 blocks (256 rows)
+  constexpr int NSLOT = 4;               // chunk c + 3 is copied while chunk c computes
+  constexpr int COPIES = 4;              // per wave and chunk
+  constexpr int STORES = 34;             // per active wave and tile: 32 of logits, 2 of partials
+  __shared__ __attribute__((aligned(16))) char smem[NSLOT * SLOT];
 
   const int n_vt = lmh_vtiles(N), n_mt = lmh_mtiles(M);
   const int x = blockIdx.x % kXcdGroup;
@@ -64,119 +140,172 @@ __global__ __launch_bounds__(512) void lmhead_logits_stats_kernel(const bf16* __
   const int n_chunks = K / kLmhKC;
   const int n_part = N / kLmhPartW;
 
-  // Waves 0-3 copy the W rows of a chunk, waves 4-7 its X rows: eight 32-row
-  // blocks each, one 16-byte copy per lane per block.
-  TileCopy<kLmhKC> tc;
-  tc.init(w & 3, lane, K);
+  // Waves 0-3 copy the W rows of a chunk, waves 4-7 its X rows: two 32-row
+  // blocks each, 16 rows per copy.  LDS row r of W block 4 v + a is vocabulary
+  // row 128 v + 4 r + a of the tile, so that the four blocks of a half give
+  // each lane four consecutive vocabulary entries; X blocks are plain.  Rows
+  // past the end (N and M are multiples of 128) are read from the tile's
+  // first 128: their results are not used.
   const bool copies_w = w < 4;
-  const bf16* src = copies_w ? W : X;
-  const int src_rows = copies_w ? N : M;
-  auto dma = [&](int tile, int c, int slot) {
+  const int cb = 2 * (w & 3);  // first of this wave's two blocks
+  const int64_t lane_row = (int64_t)(lane >> 2) * (copies_w ? 4 : 1) * K + ((lane & 3) ^ lmh_swz(lane >> 2)) * 8;
+  const bf16* lane_src = (copies_w ? W : X) + lane_row;
+  const unsigned lane_dst = lds_addr(smem) + (copies_w ? 0 : 8 * BLK) + cb * BLK;
+
+  // The copies run three chunks ahead of the contractions, across tiles (past
+  // the last tile they repeat it, into slots nobody reads).
+  const bf16* src[COPIES];  // this lane's source of each copy of the next chunk
+  int l_cp = l, left = n_chunks;
+  auto point_at = [&](int tile) {
     const int v0 = (tile >> 16) * kLmhTileV, m0 = (tile & 0xffff) * kLmhTileM;
-    const int row0 = copies_w ? v0 : m0;
-    char* b = smem + slot * SLOT + (copies_w ? 0 : 8 * TILE);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (row0 + 32 * i < src_rows) tc.copy_full(src + c * kLmhKC, row0 + 32 * i, b + i * TILE);
+    for (int i = 0; i < 2; ++i) {
+      const int blk = cb + i;
+      const int row = copies_w ? (v0 + 128 * (blk >> 2) < N ? v0 + 128 * (blk >> 2) : v0) + (blk & 3)
+                               : (m0 + 32 * blk < M ? m0 + 32 * blk : m0);
+      src[2 * i] = lane_src + (int64_t)row * K;
+      src[2 * i + 1] = src[2 * i] + (int64_t)(copies_w ? 64 : 16) * K;  // the block's rows 16 .. 31
+    }
+  };
+  auto copy = [&](int i, unsigned slot) {  // slot: byte offset
+    dma16_v(src[i], lane_dst + slot + i * 1024);
+    src[i] += kLmhKC;
+  };
+  auto copied = [&] {  // after the copies of a chunk
+    if (__builtin_expect(--left == 0, 0)) {
+      left = n_chunks;
+      l_cp = l_cp + per_xcd < n_tiles ? l_cp + per_xcd : l_cp;
+      point_at(lmh_xcd_tile(x, l_cp, n_vt, n_mt));
+    }
+  };
+  point_at(lmh_xcd_tile(x, l, n_vt, n_mt));
+#pragma unroll
+  for (int c = 0; c < NSLOT - 1; ++c) {
+#pragma unroll
+    for (int i = 0; i < COPIES; ++i) copy(i, c * SLOT);
+    copied();
+  }
+
+  // Fragment addresses of k-step 0 in the pair of slots `pair` (0 or 2 SLOT);
+  // k-step 1 is 32 bytes away (XOR).
+  const unsigned fr = r * 64 + ((h ^ lmh_swz(r)) << 4);
+  unsigned fw = fr + 4 * vw * BLK, fx = fr + (8 + 2 * tw) * BLK;
+  unsigned pair = 0;
+  MB::frag wf[2][4], xf[2][2];
+  auto read_step = [&](unsigned flip, unsigned off, int buf) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) xf[buf][t] = *(const MB::frag*)(smem + (fx ^ flip) + off + t * BLK);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) wf[buf][a] = *(const MB::frag*)(smem + (fw ^ flip) + off + a * BLK);
   };
 
   int tile = lmh_xcd_tile(x, l, n_vt, n_mt);
-  int slot = 0;
-  dma(tile, 0, 0);
+  bool stored = false;  // this wave stored a tile of logits just before
+  wait_vm(2 * COPIES);
+  asm volatile("s_barrier" ::: "memory");
+  read_step(0, 0, 0);
   while (true) {
     const int v0 = (tile >> 16) * kLmhTileV, m0 = (tile & 0xffff) * kLmhTileM;
     const int vrow = v0 + 128 * vw, tok0 = m0 + 64 * tw;
     const bool active = vrow < N && tok0 < M;  // uniform per wave
     const int l_next = l + per_xcd;
-    const int tile_next = l_next < n_tiles ? lmh_xcd_tile(x, l_next, n_vt, n_mt) : -1;
 
-    f32x16 acc[4][2];  // [vocabulary block][token block] of Z^T
+    f32x16 acc[2][4];  // [token block][vocabulary block] of Z
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int t = 0; t < 2; ++t) acc[a][t] = f32x16{};
+      for (int a = 0; a < 4; ++a) acc[t][a] = f32x16{};
 
-    for (int c = 0; c < n_chunks; ++c) {
-      // chunk c landed in `slot` (the only copy in flight); every wave is done
-      // reading the other slot, which the next copy overwrites
-      tile_barrier(0);
-      if (c + 1 < n_chunks) {
-        dma(tile, c + 1, slot ^ 1);
-      } else if (tile_next >= 0) {
-        dma(tile_next, 0, slot ^ 1);
-      }
-      if (active) {
-        // Operand fragments are double-buffered across k-steps: the reads of
-        // step ks + 1 are issued before the contractions of step ks, so each
-        // group of eight contractions runs while the next group's operands
-        // arrive instead of waiting on LDS every two contractions.
-        const char* b = smem + slot * SLOT;
-        MB::frag wf[2][4], xf[2][2];
-        auto read_step = [&](int ks, int buf) {
-#pragma unroll
-          for (int a = 0; a < 4; ++a) wf[buf][a] = read_row_frag<bf16, kLmhKC>(b + (4 * vw + a) * TILE, r, ks, h);
-#pragma unroll
-          for (int t = 0; t < 2; ++t) xf[buf][t] = read_row_frag<bf16, kLmhKC>(b + (8 + 2 * tw + t) * TILE, r, ks, h);
-        };
-        read_step(0, 0);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          if (ks + 1 < KS) read_step(ks + 1, (ks + 1) & 1);
-#pragma unroll
-          for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int t = 0; t < 2; ++t) acc[a][t] = MB::run(wf[ks & 1][a], xf[ks & 1][t], acc[a][t]);
+    // Two chunks per iteration, so that a loop iteration has no branch to
+    // take and names its slots by constants.
+    bool drain = stored;
+    for (int c = 0; c < n_chunks; c += 2) {
+      unroll<2>([&](auto odd) {
+        constexpr unsigned ODD = decltype(odd)::value;
+        // Chunk c + 1 (of the next tile after the last) has landed when only
+        // the copies of chunk c + 2 are in flight -- and, over a tile's first
+        // two chunks, the stores of the tile before, which are younger than
+        // the copies waited for (a wave's vector memory operations count in
+        // order).  The stores so get two chunks' time to drain.
+        if (__builtin_expect(drain, 0)) {
+          __builtin_amdgcn_s_waitcnt(0x0F70 | ((COPIES + STORES) & 15) | (((COPIES + STORES) >> 4) << 14));
+        } else {
+          __builtin_amdgcn_s_waitcnt(0x0F70 | COPIES);
         }
-        // issue order: steps 0 and 1's reads, then per step its eight
-        // contractions followed by the reads two steps ahead
-        static_assert(KS == 4, "the issue order below is written for four k-steps");
-        __builtin_amdgcn_sched_group_barrier(0x100, 12, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);
-      }
-      slot ^= 1;
+        asm volatile("s_barrier" ::: "memory");
+        // The slot of chunk c - 1, which every wave has read, takes chunk c + 3.
+        const unsigned to = ODD ? pair : (pair ^ 2 * SLOT) + SLOT;
+        if (active) {
+          // Operand fragments are double-buffered across k-steps and chunks:
+          // the reads of a step are issued before the contractions of the step
+          // before, and the copies between contractions, which cover them.
+          read_step(32, ODD * SLOT, 1);
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+              acc[t][a] = MB::run(xf[0][t], wf[0][a], acc[t][a]);
+              if (a & 1) {
+                __builtin_amdgcn_sched_barrier(0);
+                copy(2 * t + (a >> 1), to);
+                __builtin_amdgcn_sched_barrier(0);
+              }
+            }
+          read_step(ODD ? 2 * SLOT : 0, ODD ? 0 : SLOT, 0);  // after the last chunk of all: discarded
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) acc[t][a] = MB::run(xf[1][t], wf[1][a], acc[t][a]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < COPIES; ++i) copy(i, to);
+          if (ODD && c + 2 >= n_chunks) read_step(2 * SLOT, 0, 0);
+        }
+        copied();
+      });
+      fw ^= 2 * SLOT;
+      fx ^= 2 * SLOT;
+      pair ^= 2 * SLOT;
+      drain = false;
     }
 
-    // Epilogue.  acc[a][t][e]: Z[token tok0 + 32 t + r][vocab vrow + 32 a + acc_row(e, h)]
+    // Epilogue.  acc[t][a][e]: Z[token tok0 + 32 t + acc_row(e, h)][vocab vrow + 4 r + a]:
+    // each store writes 512 consecutive bytes of two token rows.
     if (active) {
+      const int j = lane & 15;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        const int tok = tok0 + 32 * t + r;
-        float* zrow = Z + (int64_t)tok * N + vrow;
+        float* zrow = Z + (int64_t)(tok0 + 32 * t) * N + vrow;
+        const unsigned lane_off = (unsigned)(4 * h * N + 4 * r) * 4u;
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {  // two partials of 64 entries: blocks 2p, 2p + 1
-          float mx = acc[2 * p][t][0];
-#pragma unroll
-          for (int a = 2 * p; a < 2 * p + 2; ++a)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) mx = fmaxf(mx, acc[a][t][e]);
-          mx = halves_max(mx);
-          float s = 0.f;
-#pragma unroll
-          for (int a = 2 * p; a < 2 * p + 2; ++a)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) s += exp2_hw((acc[a][t][e] - mx) * kLog2e);
-          s = halves_sum(s);
-          if (h == 0) {
-            float2* pp = (float2*)(part + ((int64_t)tok * n_part + (vrow + 64 * p) / kLmhPartW) * 2);
-            *pp = make_float2(mx, s);
-          }
+        for (int e = 0; e < 16; ++e) {
+          __builtin_nontemporal_store(f32x4{acc[t][0][e], acc[t][1][e], acc[t][2][e], acc[t][3][e]},
+                                      (f32x4*)((char*)zrow + lane_off));
+          zrow += (int64_t)(e % 4 == 3 ? 5 : 1) * N;
         }
+        float mx[16], sum[16];
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int e = 0; e < 16; ++e)
+          mx[e] = fmaxf(fmaxf(acc[t][0][e], acc[t][1][e]), fmaxf(acc[t][2][e], acc[t][3][e]));
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
-            *(f32x4*)(zrow + 32 * a + 8 * g + 4 * h) =
-                f32x4{acc[a][t][4 * g], acc[a][t][4 * g + 1], acc[a][t][4 * g + 2], acc[a][t][4 * g + 3]};
+        for (int e = 0; e < 16; e += 4) row16_max4(mx[e], mx[e + 1], mx[e + 2], mx[e + 3]);
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          sum[e] = (exp2_hw((acc[t][0][e] - mx[e]) * kLog2e) + exp2_hw((acc[t][1][e] - mx[e]) * kLog2e)) +
+                   (exp2_hw((acc[t][2][e] - mx[e]) * kLog2e) + exp2_hw((acc[t][3][e] - mx[e]) * kLog2e));
+        const int j = lane & 15;
+        const int64_t tok = tok0 + 32 * t + acc_row(j, h);
+        *(float2*)(part + (tok * n_part + vrow / kLmhPartW + (r >> 4)) * 2) =
+            make_float2(select16(mx, j), row16_sum_scatter(sum, j));
       }
     }
-    if (tile_next < 0) break;
+    stored = active;
+    if (l_next >= n_tiles) break;
     l = l_next;
-    tile = tile_next;
+    tile = lmh_xcd_tile(x, l, n_vt, n_mt);
   }
+  wait_vm(0);  // no copy may land in this LDS once another work group has it
 }
 
 // One wave per row: merge the row's partials (maximum, sum) into LSE; with
@@ -190,11 +319,27 @@ __global__ __launch_bounds__(256) void lmhead_merge_kernel(const float* __restri
   if (row >= M) return;
   const int n_part = N / kLmhPartW;
   const float2* p = (const float2*)(part + (int64_t)row * n_part * 2);
-  float m = -INFINITY;
-  for (int i = lane; i < n_part; i += 64) m = fmaxf(m, p[i].x);
-  m = wave_max(m);
-  float s = 0.f;
-  for (int i = lane; i < n_part; i += 64) s += p[i].y * exp2_hw((p[i].x - m) * kLog2e);
+  // Up to kHeld partials per lane stay in registers, all loads in flight at
+  // once (two passes over memory with one load in flight took 28 us at 8192 x
+  // 786 partials, this 12).
+  constexpr int kHeld = 16;
+  float m = -INFINITY, s = 0.f;
+  if (n_part <= 64 * kHeld) {
+    float2 v[kHeld];
+#pragma unroll
+    for (int k = 0; k < kHeld; ++k)
+      v[k] = lane + 64 * k < n_part ? p[lane + 64 * k] : make_float2(-INFINITY, 0.f);
+#pragma unroll
+    for (int k = 0; k < kHeld; ++k) m = fmaxf(m, v[k].x);
+    m = wave_max(m);
+#pragma unroll
+    for (int k = 0; k < kHeld; ++k)
+      if (lane + 64 * k < n_part) s += v[k].y * exp2_hw((v[k].x - m) * kLog2e);
+  } else {
+    for (int i = lane; i < n_part; i += 64) m = fmaxf(m, p[i].x);
+    m = wave_max(m);
+    for (int i = lane; i < n_part; i += 64) s += p[i].y * exp2_hw((p[i].x - m) * kLog2e);
+  }
   s = wave_sum(s);
   const float l = m + logf(s);
   if (lane == 0) {

@@ -9,7 +9,7 @@ namespace cattn {
 
 constexpr int kLmhTileV = 256;  // vocabulary rows per output tile
 constexpr int kLmhTileM = 256;  // tokens per output tile
-constexpr int kLmhKC = 64;      // K chunk per ring slot
+constexpr int kLmhKC = 32;      // K chunk per ring slot
 constexpr int kLmhPartW = 64;   // vocabulary entries per partial statistic
 
 constexpr int lmh_vtiles(int N) { return (N + kLmhTileV - 1) / kLmhTileV; }
