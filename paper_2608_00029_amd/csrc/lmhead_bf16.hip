@@ -131,21 +131,41 @@ __global__ __launch_bounds__(512) void lmhead_logits_stats_kernel(const bf16* __
   const int n_vt = lmh_vtiles(N), n_mt = lmh_mtiles(M);
   const int x = blockIdx.x % kXcdGroup;
   const int n_tiles = lmh_xcd_tiles(x, n_vt, n_mt);
-  int l = blockIdx.x / kXcdGroup;
-  if (l >= n_tiles) return;  // uniform over the group
-
+  const int first = blockIdx.x / kXcdGroup;
+  const int n_mine = (lmh_xcd_items(n_tiles, per_xcd) - first + per_xcd - 1) / per_xcd;  // this work group's items
+  if (n_mine <= 0) return;  // uniform over the group
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int vw = w & 1, tw = w >> 1;  // this wave: vocabulary half (128 rows), token quarter (64)
+
+  // The work group's items, 64 at a time, one per lane: the schedule's integer
+  // divisions run once for all of them, off the loop, and an item is then two
+  // lane reads (computed one by one between two tiles they cost 1 us a tile).
+  int win = -64, win_v0 = 0, win_m0 = 0;
+  int v_cut = kLmhTileV, m_cut = kLmhTileM;  // extents of the items cut from the last, partial round
+  const int n_whole = n_tiles / per_xcd;     // whole tiles of this work group; item n_whole is the cut one
+  auto item_at = [&](int k) __attribute__((always_inline)) {
+    if (k < win || k >= win + 64) {
+      win = k & ~63;
+      const LmhItem t = lmh_xcd_item(x, first + imin(win + lane, n_mine - 1) * per_xcd, n_vt, n_mt, per_xcd);
+      win_v0 = t.v0;
+      win_m0 = t.m0;
+    }
+    return LmhItem{__builtin_amdgcn_readlane(win_v0, k - win), __builtin_amdgcn_readlane(win_m0, k - win),
+                   k < n_whole ? kLmhTileV : v_cut, k < n_whole ? kLmhTileM : m_cut};
+  };
+  if (n_mine > n_whole) {
+    const LmhItem t = lmh_xcd_item(x, first + n_whole * per_xcd, n_vt, n_mt, per_xcd);
+    v_cut = t.v_ext;
+    m_cut = t.m_ext;
+  }
   const int n_chunks = K / kLmhKC;
   const int n_part = N / kLmhPartW;
 
   // Waves 0-3 copy the W rows of a chunk, waves 4-7 its X rows: two 32-row
   // blocks each, 16 rows per copy.  LDS row r of W block 4 v + a is vocabulary
   // row 128 v + 4 r + a of the tile, so that the four blocks of a half give
-  // each lane four consecutive vocabulary entries; X blocks are plain.  Rows
-  // past the end (N and M are multiples of 128) are read from the tile's
-  // first 128: their results are not used.
+  // each lane four consecutive vocabulary entries; X blocks are plain.
   const bool copies_w = w < 4;
   const int cb = 2 * (w & 3);  // first of this wave's two blocks
   const int64_t lane_row = (int64_t)(lane >> 2) * (copies_w ? 4 : 1) * K + ((lane & 3) ^ lmh_swz(lane >> 2)) * 8;
@@ -155,14 +175,17 @@ __global__ __launch_bounds__(512) void lmhead_logits_stats_kernel(const bf16* __
   // The copies run three chunks ahead of the contractions, across tiles (past
   // the last tile they repeat it, into slots nobody reads).
   const bf16* src[COPIES];  // this lane's source of each copy of the next chunk
-  int l_cp = l, left = n_chunks;
-  auto point_at = [&](int tile) {
-    const int v0 = (tile >> 16) * kLmhTileV, m0 = (tile & 0xffff) * kLmhTileM;
+  int k_cp = 0, left = n_chunks;
+  auto point_at = [&](const LmhItem t) __attribute__((always_inline)) {
+    // Rows past the end of the item (N and M are multiples of 128) are read
+    // from its first ones, or from row 0 if it has none: results not used.
+    const int vb = t.v0 < N ? t.v0 : 0, mb = t.m0 < M ? t.m0 : 0;
+    const int v_end = imin(vb + t.v_ext, N), m_end = imin(mb + t.m_ext, M);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int blk = cb + i;
-      const int row = copies_w ? (v0 + 128 * (blk >> 2) < N ? v0 + 128 * (blk >> 2) : v0) + (blk & 3)
-                               : (m0 + 32 * blk < M ? m0 + 32 * blk : m0);
+      const int row = copies_w ? (vb + 128 * (blk >> 2) < v_end ? vb + 128 * (blk >> 2) : vb) + (blk & 3)
+                               : (mb + 32 * blk < m_end ? mb + 32 * blk : mb);
       src[2 * i] = lane_src + (int64_t)row * K;
       src[2 * i + 1] = src[2 * i] + (int64_t)(copies_w ? 64 : 16) * K;  // the block's rows 16 .. 31
     }
@@ -171,14 +194,14 @@ __global__ __launch_bounds__(512) void lmhead_logits_stats_kernel(const bf16* __
     dma16_v(src[i], lane_dst + slot + i * 1024);
     src[i] += kLmhKC;
   };
-  auto copied = [&] {  // after the copies of a chunk
+  auto copied = [&]() __attribute__((always_inline)) {  // after the copies of a chunk
     if (__builtin_expect(--left == 0, 0)) {
       left = n_chunks;
-      l_cp = l_cp + per_xcd < n_tiles ? l_cp + per_xcd : l_cp;
-      point_at(lmh_xcd_tile(x, l_cp, n_vt, n_mt));
+      k_cp = imin(k_cp + 1, n_mine - 1);
+      point_at(item_at(k_cp));
     }
   };
-  point_at(lmh_xcd_tile(x, l, n_vt, n_mt));
+  point_at(item_at(0));
 #pragma unroll
   for (int c = 0; c < NSLOT - 1; ++c) {
 #pragma unroll
@@ -199,16 +222,15 @@ __global__ __launch_bounds__(512) void lmhead_logits_stats_kernel(const bf16* __
     for (int a = 0; a < 4; ++a) wf[buf][a] = *(const MB::frag*)(smem + (fw ^ flip) + off + a * BLK);
   };
 
-  int tile = lmh_xcd_tile(x, l, n_vt, n_mt);
   bool stored = false;  // this wave stored a tile of logits just before
   wait_vm(2 * COPIES);
   asm volatile("s_barrier" ::: "memory");
   read_step(0, 0, 0);
-  while (true) {
-    const int v0 = (tile >> 16) * kLmhTileV, m0 = (tile & 0xffff) * kLmhTileM;
-    const int vrow = v0 + 128 * vw, tok0 = m0 + 64 * tw;
-    const bool active = vrow < N && tok0 < M;  // uniform per wave
-    const int l_next = l + per_xcd;
+  for (int k = 0; k < n_mine; ++k) {
+    const LmhItem item = item_at(k);
+    const int vrow = item.v0 + 128 * vw, tok0 = item.m0 + 64 * tw;
+    // uniform per wave
+    const bool active = vrow < imin(item.v0 + item.v_ext, N) && tok0 < imin(item.m0 + item.m_ext, M);
 
     f32x16 acc[2][4];  // [token block][vocabulary block] of Z
 #pragma unroll
@@ -301,9 +323,6 @@ __global__ __launch_bounds__(512) void lmhead_logits_stats_kernel(const bf16* __
       }
     }
     stored = active;
-    if (l_next >= n_tiles) break;
-    l = l_next;
-    tile = lmh_xcd_tile(x, l, n_vt, n_mt);
   }
   wait_vm(0);  // no copy may land in this LDS once another work group has it
 }
