@@ -44,9 +44,6 @@ constexpr int kBwdNbSplit = 4;   // dQ and dK/dV at D = 64 with the loop range i
 constexpr int kFwdGroup = 2;     // iterations per barrier, where the ring is deep enough (ring_group)
 constexpr int kDqGroup = 2;
 constexpr int kDkdvGroup = 2;
-// The backward at D = 64 splits each tile's loop range in two when the unsplit
-// grid would fill fewer than this many work-group slots per CU.
-constexpr int kBwdSplitWgPerCu = 2;
 
 // Causal loop clamping (section 4.2): the loops visit only the tiles that hold
 // visible (query, key) pairs -- the forward and dQ loops stop at the diagonal,
@@ -72,11 +69,11 @@ constexpr float kSumMax = 4294967296.0f;
 //
 // A workgroup owns 32*QG queries of one (batch, head), QG = 4/SPLIT query
 // groups of 32 (one per wave), and splits the keys it must visit into SPLIT
-// consecutive parts: wave w takes query group w % QG and key part w / QG.
-// Each part streams its own ring of K/V tiles, so the sequential chain of a
-// wave is 1/SPLIT of the key range (the critical path of the causal grid is
-// its heaviest query tile).  With SPLIT = 2 the two partial results of a
-// query group -- (O, running offset, running sum) -- merge lane to lane
+// interleaved parts (tile t belongs to part t % SPLIT): wave w takes query
+// group w % QG and key part w / QG.  Each part streams its own ring of K/V
+// tiles, so the sequential chain of a wave is 1/SPLIT of the key range (the
+// critical path of the causal grid is its heaviest query tile).  The partial
+// results of a query group -- (O, running offset, running sum) -- merge
 // through LDS at the end with the usual rescale-by-offset-difference rule.
 //
 // Online softmax in base 2 with a lazily moved offset: the exponentials of a
@@ -86,8 +83,11 @@ constexpr float kSumMax = 4294967296.0f;
 // computes the block max, moves m, rescales O and the running sum, and redoes
 // the block.  No per-block max is computed on the common path.
 // ---------------------------------------------------------------------------
+// Whether each block runs start to end in its iteration: all forms but the
+// two-part one at D = 64.
+template <int D, int SPLIT> constexpr bool fwd_lean() { return !(D == 64 && SPLIT == 2); }
 template <int D, bool CAUSAL, int SPLIT, int NB, bool RAG>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT == 1 ? (D == 128 ? 3 : 4) : 1, 10)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT == 1 ? (D == 128 ? 3 : 4) : fwd_lean<D, SPLIT>() ? 2 : 1, 10)))
 void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                                                             const bf16* __restrict__ V, bf16* __restrict__ O,
                                                             float* __restrict__ LSE, int S, int BH, int n_qtiles,
@@ -98,7 +98,8 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
   constexpr int KS_D = D / 16, DT = D / 32;
   constexpr int PER_TILE = 2 * G::DMA_PER_TENSOR;
   __shared__ __attribute__((aligned(16))) char smem[SPLIT * NB * SET];  // [part][slot][K, V]
-  static_assert(SPLIT == 1 || 2 * 64 * (2 * DT * 16 + 2) * 4 <= SPLIT * NB * SET, "merge area");
+  __shared__ float stats[2][4][SPLIT > 1 ? 64 : 1];                     // each wave's offset and sum, for the merge
+  static_assert(SPLIT == 1 || 4 * 64 * DT * 16 * 4 <= SPLIT * NB * SET, "merge area");
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index: uniform, kept in an SGPR
@@ -114,21 +115,22 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
   const int q0 = qt * BQ, qw = q0 + 32 * qg, my_q = qw + r;
   const int kend = CAUSAL && !kNoClamp ? min(S, q0 + BQ) : S;   // causal loop clamping (workgroup)
   const int n = (kend + 31) / 32;                   // 32-key tiles of the workgroup
-  const int L = (n + SPLIT - 1) / SPLIT;            // tiles per part (the last may be short)
+  const int L = (n + SPLIT - 1) / SPLIT;            // iterations; part p owns tiles p, p + SPLIT, ...
   const int kend_w = qw >= S ? 0 : (CAUSAL && !kNoClamp ? min(S, qw + 32) : S);
-  const int nsb = (kend_w + 31) / 32;               // tiles this wave's queries need
-  const int tb = part * L;                          // this wave's tiles: [tb, te)
-  const int te = min(nsb, min(n, tb + L));
-  const int cnt = te > tb ? te - tb : 0;
+  const int nsb = (kend_w + 31) / 32;               // tiles this wave's queries need: [0, nsb)
+  // (Without the clamp a part that owns no visible tile stays idle as well:
+  // it would have no real score to set the softmax offset from.)
+  const bool idle = part >= nsb || (CAUSAL && kNoClamp && part > qw / 32);
+  const int cnt = idle ? 0 : (nsb - part + SPLIT - 1) / SPLIT;  // this wave's iterations
 
-  const int n_last = n - (SPLIT - 1) * L;  // tiles of the last part (<= L)
   // the key tile that holds the ragged end of the sequence, if this workgroup copies one
   const int t_rag = RAG && (S - 1) / 32 < n ? (S - 1) / 32 : -1;
-  // the iteration (in this wave's part) whose tile must be masked: the wave's
-  // last tile when it straddles the causal diagonal or the end of the sequence
-  // (without the clamp, every tile from the one holding the diagonal on: i >= i_mask)
-  const int i_mask = CAUSAL && kNoClamp ? qw / 32 - tb
-                     : nsb > 0 && ((CAUSAL && (nsb - 1) * 32 + 31 > qw) || nsb * 32 > S) ? nsb - 1 - tb : -1;
+  // the iteration whose tile must be masked: the wave's last when it straddles
+  // the causal diagonal or the end of the sequence (without the clamp, every
+  // tile from the one holding the diagonal on: i >= i_mask)
+  const bool masked_last = nsb > 0 && ((CAUSAL && (nsb - 1) * 32 + 31 > qw) || nsb * 32 > S);
+  const int i_mask = CAUSAL && kNoClamp ? (qw / 32 + SPLIT - 1 - part) / SPLIT
+                     : masked_last && (nsb - 1) % SPLIT == part ? (nsb - 1) / SPLIT : -1;
 
   TileCopy<D> tc;
   tc.init(w, lane, rs);
@@ -136,28 +138,26 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
   auto dma = [&](int x, auto slc) {  // iteration x's tile of every part, into ring slot slc
 #pragma unroll
     for (int p = 0; p < SPLIT; ++p) {
-      if (p < SPLIT - 1 || x < n_last) {
-        const int t = p * L + x;
-        char* dst = smem + (p * NB + decltype(slc)::value) * SET;
-        if (!RAG || t != t_rag) {
-          tc.copy_full(Kb, t * 32, dst);
-          tc.copy_full(Vb, t * 32, dst + TILE);
-        } else {
-          tc.copy(Kb, t * 32, S, dst);
-          tc.copy(Vb, t * 32, S, dst + TILE);
-        }
+      const int t = SPLIT == 1 ? x : min(x * SPLIT + p, n - 1);  // (a part without a last tile copies another's)
+      char* dst = smem + (p * NB + decltype(slc)::value) * SET;
+      if (!RAG || t != t_rag) {
+        tc.copy_full(Kb, t * 32, dst);
+        tc.copy_full(Vb, t * 32, dst + TILE);
+      } else {
+        tc.copy(Kb, t * 32, S, dst);
+        tc.copy(Vb, t * 32, S, dst + TILE);
       }
     }
   };
-  // Unsplit grids: each block runs start to end in its iteration (no score
-  // block computed ahead) with every K and V fragment read from LDS one
-  // contraction step before its use, which leaves room for four waves per SIMD
-  // at D = 64 (110 registers) and three at D = 128.  Split grids compute
-  // S(j+1) while the softmax of S(j) runs.
-  constexpr bool LEANF = SPLIT == 1;
+  // LEANF: each block runs start to end in its iteration (no score block
+  // computed ahead) with every K and V fragment read from LDS one contraction
+  // step before its use, which leaves room for four waves per SIMD at D = 64
+  // (110 registers) and three at D = 128.  The form in two parts at D = 64
+  // computes S(j+1) while the softmax of S(j) runs.
+  constexpr bool LEANF = fwd_lean<D, SPLIT>();
   constexpr int NEED = LEANF ? 0 : 1;  // iteration i reads the tiles of iterations i .. i+NEED
   constexpr int GROUP = ring_group(SPLIT, NB, NEED, kFwdGroup);  // iterations per barrier
-  static_assert(!LEANF || SPLIT * NB * SET <= 65536, "tile reads reach every slot by immediate offset");
+  static_assert(!LEANF || NB * SET <= 65536, "tile reads reach every slot by immediate offset");
   ring_prologue<NB, GROUP>(L, dma);
   Frag128 fo;
   if constexpr (LEANF && D == 128) fo.init(r, h, lane);
@@ -218,7 +218,7 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
       constexpr int pc = PAR ? (sl & 1) : 0, pn = PAR ? (pc ^ 1) : 1;
       const int i = i0 + sl;
       if (i >= L) return;
-      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, n_last, dma);
+      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, L, dma);
       if (i >= cnt) return;  // wave-uniform: this wave is done, it only keeps the barriers
       if constexpr (LEANF) {
         const char* kt = ring + sl * SET;
@@ -231,7 +231,7 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
           s = MB::run(ka[ks & 1], qf[ks], s);
         }
         if (CAUSAL && kNoClamp ? i >= i_mask : i == i_mask) {
-          const int k0 = (tb + i) * 32;
+          const int k0 = (i * SPLIT + part) * 32;
 #pragma unroll
           for (int a = 0; a < 16; ++a) {
             const int key = k0 + acc_row(a, h);
@@ -270,7 +270,7 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
       f32x16& sa_ = sa[pc];
       // causal diagonal / ragged end: only the last tile of the wave's queries
       if (CAUSAL && kNoClamp ? i >= i_mask : i == i_mask) {
-        const int k0 = (tb + i) * 32;
+        const int k0 = (i * SPLIT + part) * 32;
 #pragma unroll
         for (int a = 0; a < 16; ++a) {
           const int key = k0 + acc_row(a, h);
@@ -345,37 +345,51 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
     }
   }
 
-  if constexpr (SPLIT == 2) {
-    // Merge the two key parts of each query group: part 1 hands (O, m, l) to
-    // part 0 through LDS, lane to lane (both waves share the same lane layout).
+  bf16* orow = O + base + (int64_t)my_q * rs;
+  if constexpr (SPLIT > 1) {
+    // Merge the parts of each query group through LDS, each wave finishing a
+    // share of the columns.  A part that saw no tile has the offset kMasked,
+    // whose scale is exactly 0, and O = l = 0.
     wait_vm(0);
     __syncthreads();  // every wave is done with the rings
-    float* xb = (float*)smem + (size_t)qg * 64 * (2 * DT * 16 + 2);
-    if (part == 1) {
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int a = 0; a < 16; ++a) xb[(dt * 16 + a) * 64 + lane] = oacc[dt][a];
-      xb[(DT * 16) * 64 + lane] = m;
-      xb[(DT * 16 + 1) * 64 + lane] = lsum;
-    }
+    f32x4* area = (f32x4*)smem;
+    put_partial<D>(area, w, lane, oacc);
+    stats[0][w][lane] = m;
+    stats[1][w][lane] = lsum;
     __syncthreads();
-    if (part == 1) return;
-    const float m1 = xb[(DT * 16) * 64 + lane], l1 = xb[(DT * 16 + 1) * 64 + lane];
-    const float mn = fmaxf(m, m1);
-    const float s0 = exp2_hw((m - mn) * c), s1 = exp2_hw((m1 - mn) * c);
+    if (my_q >= S) return;
+    float sp[SPLIT], mn = kMasked;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int p = 0; p < SPLIT; ++p) {
+      sp[p] = stats[0][qg + p * QG][lane];
+      mn = fmaxf(mn, sp[p]);
+    }
+    float l = 0.f;
 #pragma unroll
-      for (int a = 0; a < 16; ++a) oacc[dt][a] = oacc[dt][a] * s0 + xb[(dt * 16 + a) * 64 + lane] * s1;
-    lsum = lsum * s0 + l1 * s1;
-    m = mn;
+    for (int p = 0; p < SPLIT; ++p) {
+      sp[p] = exp2_hw((sp[p] - mn) * c);
+      l += stats[1][qg + p * QG][lane] * sp[p];
+    }
+    l = halves_sum(l);
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int gi = 0; gi < QG; ++gi) {
+      const int g = part * QG + gi;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        f32x4 v = get_partial<D>(area, qg, dt, g, lane) * sp[0];
+#pragma unroll
+        for (int p = 1; p < SPLIT; ++p) v += get_partial<D>(area, qg + p * QG, dt, g, lane) * sp[p];
+        store4<bf16>(orow + dt * 32 + 8 * g + 4 * h, v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
+      }
+    }
+    if (part == 0 && h == 0) LSE[(int64_t)bh * S + my_q] = (mn * c + log2f(l)) * kLn2;
+    return;
   }
 
   const float l = halves_sum(lsum);
   if (my_q < S) {
     const float inv = 1.0f / l;
-    bf16* orow = O + base + (int64_t)my_q * rs;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -386,15 +400,40 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
   }
 }
 
+// Sum of the parts' accumulators in part order, through `area`, times f, to
+// this lane's output row (if `valid`); each wave finishes its share of the
+// columns.  Every wave calls it; the area may hold data other waves still read.
+template <int D, int G>
+__device__ __forceinline__ void sum_parts_and_store(f32x4* area, int w, int h, int lane, const f32x16 (&acc)[D / 32],
+                                                    bf16* row, bool valid, float f) {
+  constexpr int SPLIT = 4 / G;
+  const int grp = w % G, part = w / G;
+  __syncthreads();
+  put_partial<D>(area, w, lane, acc);
+  __syncthreads();
+  if (!valid) return;
+#pragma unroll
+  for (int gi = 0; gi < G; ++gi) {
+    const int g = part * G + gi;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) {
+      f32x4 v = get_partial<D>(area, grp, dt, g, lane);
+#pragma unroll
+      for (int p = 1; p < SPLIT; ++p) v += get_partial<D>(area, grp + p * G, dt, g, lane);
+      store4<bf16>(row + dt * 32 + 8 * g + 4 * h, v[0] * f, v[1] * f, v[2] * f, v[3] * f);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Backward, kernel 1: dQ (reduces over keys).  Also writes, per (batch, head),
 // D = rowsum(dO * O) and -LSE/scale into the workspace (rows padded to a
 // multiple of 32 with zeros) for the dK/dV kernel to copy by DMA.
 //
 // Like the forward, a workgroup owns 32*QG queries (QG = 4/SPLIT query groups
-// of 32, one per wave) and splits the keys it must visit into SPLIT parts,
-// each streaming its own ring of K/V tiles; with SPLIT = 2 the two partial
-// dQ are added through LDS at the end.
+// of 32, one per wave) and splits the keys it must visit into SPLIT
+// interleaved parts, each streaming its own ring of K/V tiles; the partial dQ
+// are added through LDS at the end.
 //
 // dS = P (dP - D) takes one multiply per element: the dP contraction starts
 // from an accumulator holding D and multiplies by -dO, so it yields D - dP.
@@ -413,7 +452,7 @@ void attn_bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict_
   constexpr int KS_D = D / 16, DT = D / 32;
   constexpr int PER_TILE = 2 * G::DMA_PER_TENSOR;
   __shared__ __attribute__((aligned(16))) char smem[SPLIT * NB * SET];  // [part][slot][K, V]
-  static_assert(SPLIT == 1 || QG * 64 * (DT * 16) * 4 <= SPLIT * NB * SET, "merge area");
+  static_assert(SPLIT == 1 || 4 * 64 * DT * 16 * 4 <= SPLIT * NB * SET, "merge area");
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index: uniform, kept in an SGPR
@@ -428,39 +467,35 @@ void attn_bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict_
   const int Sp = ws_rows(S);
 
   const int q0 = qt * BQ, qw = q0 + 32 * qg, my_q = qw + r;
-  const int kend = CAUSAL && !kNoClamp ? min(S, q0 + BQ) : S;
-  const int n = (kend + 31) / 32;          // 32-key tiles of the workgroup
-  const int L = (n + SPLIT - 1) / SPLIT;   // tiles per part (the last may be short)
+  const int kend = CAUSAL && !kNoClamp ? min(S, q0 + BQ) : S;   // causal loop clamping (workgroup)
+  const int n = (kend + 31) / 32;                   // 32-key tiles of the workgroup
+  const int L = (n + SPLIT - 1) / SPLIT;            // iterations; part p owns tiles p, p + SPLIT, ...
   const int kend_w = qw >= S ? 0 : (CAUSAL && !kNoClamp ? min(S, qw + 32) : S);
-  const int nsb = (kend_w + 31) / 32;      // tiles this wave's queries need
-  const int tb = part * L;                 // this wave's tiles: [tb, te)
-  const int te = min(nsb, min(n, tb + L));
-  const int cnt = te > tb ? te - tb : 0;
+  const int nsb = (kend_w + 31) / 32;               // tiles this wave's queries need: [0, nsb)
+  const int cnt = part < nsb ? (nsb - part + SPLIT - 1) / SPLIT : 0;  // this wave's iterations
 
-  const int n_last = n - (SPLIT - 1) * L;  // tiles of the last part (<= L)
   // the key tile that holds the ragged end of the sequence, if this workgroup copies one
   const int t_rag = RAG && (S - 1) / 32 < n ? (S - 1) / 32 : -1;
-  // the iteration (in this wave's part) whose tile must be masked: the wave's
-  // last tile when it straddles the causal diagonal or the end of the sequence
-  // (without the clamp, every tile from the one holding the diagonal on: i >= i_mask)
-  const int i_mask = CAUSAL && kNoClamp ? qw / 32 - tb
-                     : nsb > 0 && ((CAUSAL && (nsb - 1) * 32 + 31 > qw) || nsb * 32 > S) ? nsb - 1 - tb : -1;
+  // the iteration whose tile must be masked: the wave's last when it straddles
+  // the causal diagonal or the end of the sequence (without the clamp, every
+  // tile from the one holding the diagonal on: i >= i_mask)
+  const bool masked_last = nsb > 0 && ((CAUSAL && (nsb - 1) * 32 + 31 > qw) || nsb * 32 > S);
+  const int i_mask = CAUSAL && kNoClamp ? (qw / 32 + SPLIT - 1 - part) / SPLIT
+                     : masked_last && (nsb - 1) % SPLIT == part ? (nsb - 1) / SPLIT : -1;
 
   TileCopy<D> tc;
   tc.init(w, lane, rs);
   auto dma = [&](int x, auto slc) {  // iteration x's tile of every part, into ring slot slc
 #pragma unroll
     for (int p = 0; p < SPLIT; ++p) {
-      if (p < SPLIT - 1 || x < n_last) {
-        const int t = p * L + x;
-        char* dst = smem + (p * NB + decltype(slc)::value) * SET;
-        if (!RAG || t != t_rag) {
-          tc.copy_full(Kb, t * 32, dst);
-          tc.copy_full(Vb, t * 32, dst + TILE);
-        } else {
-          tc.copy(Kb, t * 32, S, dst);
-          tc.copy(Vb, t * 32, S, dst + TILE);
-        }
+      const int t = SPLIT == 1 ? x : min(x * SPLIT + p, n - 1);  // (a part without a last tile copies another's)
+      char* dst = smem + (p * NB + decltype(slc)::value) * SET;
+      if (!RAG || t != t_rag) {
+        tc.copy_full(Kb, t * 32, dst);
+        tc.copy_full(Vb, t * 32, dst + TILE);
+      } else {
+        tc.copy(Kb, t * 32, S, dst);
+        tc.copy(Vb, t * 32, S, dst + TILE);
       }
     }
   };
@@ -513,9 +548,9 @@ void attn_bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict_
       constexpr int sl = decltype(slc)::value;
       const int i = i0 + sl;
       if (i >= L) return;
-      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, n_last, dma);
+      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, L, dma);
       if (i >= cnt) return;  // wave-uniform: this wave is done, it only keeps the barriers
-      const int j = tb + i;  // key tile of this iteration
+      const int j = i * SPLIT + part;  // key tile of this iteration
       const char* cur = ring + sl * SET;
       if constexpr (STR) {
         // D broadcast into the dP accumulator here, not kept in 16 registers
@@ -597,24 +632,10 @@ void attn_bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict_
     });
   }
 
-  if constexpr (SPLIT == 2) {
-    // Add the two key parts of each query group: part 1 hands dQ to part 0
-    // through LDS, lane to lane (both waves share the same lane layout).
-    wait_vm(0);
-    __syncthreads();  // every wave is done with the rings
-    float* xb = (float*)smem + (size_t)qg * 64 * (DT * 16);
-    if (part == 1) {
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int a = 0; a < 16; ++a) xb[(dt * 16 + a) * 64 + lane] = dqacc[dt][a];
-    }
-    __syncthreads();
-    if (part == 1) return;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int a = 0; a < 16; ++a) dqacc[dt][a] += xb[(dt * 16 + a) * 64 + lane];
+  if constexpr (SPLIT > 1) {
+    wait_vm(0);  // the rings' last copies; then every wave adds its share of the parts
+    sum_parts_and_store<D, QG>((f32x4*)smem, w, h, lane, dqacc, dQ + base + (int64_t)my_q * rs, my_q < S, scale);
+    return;
   }
 
   if (my_q < S) {
@@ -636,24 +657,24 @@ void attn_bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict_
 //
 // A workgroup owns 32*KG keys of one (batch, head), KG = 4/SPLIT key groups of
 // 32 (one per wave), and splits the query tiles it must visit into SPLIT
-// consecutive parts: wave w takes key group w % KG and query part w / KG.
+// interleaved parts: wave w takes key group w % KG and query part w / KG.
 // Each part streams its own ring of Q/dO tiles, so the sequential chain of a
 // wave is 1/SPLIT of the query range (the heaviest causal key tile sees every
-// query tile).  With SPLIT = 2 the partial dK, dV of the two parts are added
-// lane to lane through LDS at the end (fixed order: deterministic, no atomics).
+// query tile).  The parts' dK, dV are added through LDS at the end (fixed
+// order: deterministic, no atomics).
 //
 // Every per-iteration decision is a compare against an index computed once
 // per wave (the first and last active iteration, the one holding the causal
 // diagonal, the ragged tile), and every wave issues the same copies per tile,
 // so that the common wait at the barrier is a compile-time count.
 // ---------------------------------------------------------------------------
-// dK/dV at D = 64, unsplit: operands read where they are used instead of one
+// dK/dV at D = 64, unsplit or in four parts: operands read where they are used instead of one
 // tile ahead, which gives three waves per SIMD.  At D = 128 (STREAM below) each
 // operand fragment is read one contraction step before its use, which gives
-// two; split grids at D = 64 read the next tile's rows one tile ahead.
+// two; in two parts at D = 64 the next tile's rows are read one tile ahead.
 template <int D, bool CAUSAL, int SPLIT, int NB>
 constexpr bool dkdv_lean() {
-  return D == 64 && SPLIT == 1;
+  return D == 64 && SPLIT != 2;
 }
 template <int D, bool CAUSAL, int SPLIT, int NB, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dkdv_lean<D, CAUSAL, SPLIT, NB>() ? 3 : (D == 128 ? 2 : 1), 10)))
@@ -670,7 +691,7 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
   // D = 128: every operand fragment read from LDS one contraction step before
   // its use, so that the K, V, dK and dV fragments (192 registers) and the two
   // score blocks leave room for two waves per SIMD
-  constexpr bool STREAM = D == 128 && SPLIT == 1;
+  constexpr bool STREAM = D == 128;
   constexpr int KG = 4 / SPLIT, BKV = 32 * KG;
   constexpr int TILE = G::TILE;
   constexpr int KS_D = D / 16, DT = D / 32;
@@ -685,8 +706,8 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
   constexpr int PER_TILE = 2 * G::DMA_PER_TENSOR + 1;
   // [part][slot] Q, dO tiles, then [part][slot] -LSE/scale and D rows
   __shared__ __attribute__((aligned(16))) char smem[SPLIT * NB * BUF];
-  static_assert(SPLIT == 1 || KG * 64 * (4 * DT * 16) * 4 <= SPLIT * NB * BUF, "merge area");
-  static_assert(!STREAM || AUX0 <= 65536, "tile reads reach every slot by immediate offset");
+  static_assert(SPLIT == 1 || 4 * 64 * DT * 16 * 4 <= SPLIT * NB * BUF, "merge area");
+  static_assert(!STREAM || NB * SETB <= 65536, "tile reads reach every slot by immediate offset");
 
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index: uniform, kept in an SGPR
@@ -716,39 +737,34 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
   const int nt = (S + 31) / 32;                 // query tiles of the sequence
   const int jt0 = CAUSAL && !kNoClamp ? k0 / 32 : 0;
   const int n = nt - jt0;
-  const int L = (n + SPLIT - 1) / SPLIT;        // iterations; part p owns walk positions [p*L, min(n, p*L + L))
-  const int n_last = n - (SPLIT - 1) * L;       // tiles of the last part (<= L)
-  const int jb = CAUSAL && !kNoClamp ? kw / 32 : 0;  // this wave's first query tile
-  const int je = kw >= S ? jb : nt;             // ... and one past its last
-  const int tb = part * L;                      // this wave's part starts at walk position tb
-  // iteration indices, relative to this wave's part: the wave's tiles jb .. je-1
-  // sit at walk positions nt - je .. nt - 1 - jb
-  const int i_lo = max(0, nt - je - tb);                                             // first active
-  const int i_span = max(0, min(part == SPLIT - 1 ? n_last : L, nt - jb - tb) - i_lo);  // active count
-  // causal diagonal (without the clamp, the tiles before it come after it in the walk: i >= i_diag)
-  const int i_diag = CAUSAL ? nt - 1 - kw / 32 - tb : -1;
-  const int t_rag = RAG ? 0 : -1;               // walk position of the ragged (last) tile
-  const int i_rag = t_rag - tb;                  // ... in this part
-  // copies: iteration x of the ring holds walk position p*L + x of every part p with x < L (x < n_last for the last)
+  const int L = (n + SPLIT - 1) / SPLIT;        // iterations; part p owns walk positions p, p + SPLIT, ...
+  const int jb = CAUSAL && !kNoClamp ? kw / 32 : 0;  // this wave's first query tile; its last is nt - 1
+  // this wave's iterations: its walk positions are 0 .. nt - 1 - jb (none past the end of the sequence)
+  const int cnt = kw < S && part < nt - jb ? (nt - jb - part + SPLIT - 1) / SPLIT : 0;
+  // the iteration holding the causal diagonal (without the clamp, the tiles
+  // before it come after it in the walk: i >= i_diag)
+  const int w_diag = nt - 1 - kw / 32;
+  const int i_diag = !CAUSAL || kw >= S ? -1 : kNoClamp ? (w_diag + SPLIT - 1 - part) / SPLIT
+                     : w_diag % SPLIT == part ? w_diag / SPLIT : -1;
+  const int t_rag = RAG ? 0 : -1;                // walk position of the ragged (last) tile
+  const int i_rag = RAG && part == 0 ? 0 : -1;   // ... in this part
 
   TileCopy<D> tc;
   tc.init(w, lane, rs);
   auto dma = [&](int x, auto slc) {  // iteration x's tile of every part, into ring slot slc
 #pragma unroll
     for (int p = 0; p < SPLIT; ++p) {
-      if (p < SPLIT - 1 || x < n_last) {
-        const int t = p * L + x;
-        const int row0 = (nt - 1 - t) * 32;
-        char* b = smem + (p * NB + decltype(slc)::value) * SETB;
-        if (!RAG || t != t_rag) {
-          tc.copy_full(Qb, row0, b);
-          tc.copy_full(dOb, row0, b + TILE);
-        } else {
-          tc.copy(Qb, row0, S, b);
-          tc.copy(dOb, row0, S, b + TILE);
-        }
-        if (lane < 4) dma16(wsh + row0, ld_voff, lds_addr(smem + AUX0 + (p * NB + decltype(slc)::value) * AUX) + 64 * w);
+      const int t = SPLIT == 1 ? x : min(x * SPLIT + p, n - 1);  // (a part without a last tile copies another's)
+      const int row0 = (nt - 1 - t) * 32;
+      char* b = smem + (p * NB + decltype(slc)::value) * SETB;
+      if (!RAG || t != t_rag) {
+        tc.copy_full(Qb, row0, b);
+        tc.copy_full(dOb, row0, b + TILE);
+      } else {
+        tc.copy(Qb, row0, S, b);
+        tc.copy(dOb, row0, S, b + TILE);
       }
+      if (lane < 4) dma16(wsh + row0, ld_voff, lds_addr(smem + AUX0 + (p * NB + decltype(slc)::value) * AUX) + 64 * w);
     }
   };
   constexpr int NEED = LEAN || STREAM ? 0 : 1;  // iteration i reads the tiles of iterations i .. i+NEED
@@ -781,8 +797,8 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
       constexpr int sl = decltype(slc)::value, sn = (sl + 1) % NB;
       const int i = i0 + sl;
       if (i >= L) return;
-      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, n_last, dma);
-      if ((unsigned)(i - i_lo) >= (unsigned)i_span) return;  // wave-uniform: not an active sub-block
+      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, L, dma);
+      if (i >= cnt) return;  // wave-uniform: this wave is done, it only keeps the barriers
       const char* lq = ring + sl * SETB;
       const char* ldo = lq + TILE;
       const float* llse = (const float*)(aux + sl * AUX);
@@ -793,7 +809,7 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
         read_rows<D>(lq, r, h, qf);
         read_rows<D>(ldo, r, h, dof);
       } else if constexpr (!STREAM) {
-        if (i == i_lo) {  // a wave's first sub-block: read it here
+        if (i == 0) {  // a wave's first sub-block: read it here
           read_rows<D>(lq, r, h, qf);
           read_rows<D>(ldo, r, h, dof);
         }
@@ -835,7 +851,7 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
       }
       // s[a], dx[a]: S - LSE/scale and D - dP of query 32j + acc_row(a, h), key my_k
       if ((CAUSAL && kNoClamp ? i >= i_diag : i == i_diag) || (RAG && i == i_rag)) {  // diagonal or ragged end
-        const int qs = (nt - 1 - tb - i) * 32;
+        const int qs = (nt - 1 - (i * SPLIT + part)) * 32;
 #pragma unroll
         for (int a = 0; a < 16; ++a) {
           const int qry = qs + acc_row(a, h);
@@ -896,30 +912,12 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
     });
   }
 
-  if constexpr (SPLIT == 2) {
-    // Add the two query parts of each key group: part 1 hands (dK, dV) to
-    // part 0 through LDS, lane to lane (both waves share the same lane layout).
-    wait_vm(0);
-    __syncthreads();  // every wave is done with the rings
-    float* xb = (float*)smem + (size_t)kg * 64 * (4 * DT * 16);
-    if (part == 1) {
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int a = 0; a < 16; ++a) {
-          xb[(dt * 16 + a) * 64 + lane] = dkacc[dt][a];
-          xb[((DT + dt) * 16 + a) * 64 + lane] = dvacc[dt][a];
-        }
-    }
-    __syncthreads();
-    if (part == 1) return;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int a = 0; a < 16; ++a) {
-        dkacc[dt][a] += xb[(dt * 16 + a) * 64 + lane];
-        dvacc[dt][a] += xb[((DT + dt) * 16 + a) * 64 + lane];
-      }
+  if constexpr (SPLIT > 1) {
+    wait_vm(0);  // the rings' last copies; then every wave adds its share of the parts
+    const int64_t row = base + (int64_t)my_k * rs;
+    sum_parts_and_store<D, KG>((f32x4*)smem, w, h, lane, dkacc, dK + row, my_k < S, scale);
+    sum_parts_and_store<D, KG>((f32x4*)smem, w, h, lane, dvacc, dV + row, my_k < S, 1.f);
+    return;
   }
 
   if (my_k < S) {
@@ -952,15 +950,40 @@ int cu_count() {
   return cached[dev];
 }
 
-// Forward ring depths: per key part when the key range is split in two (two
-// rings of 3 fit the LDS budget of three workgroups per CU), and unsplit.
-template <int D> struct FwdCfg {
-  static constexpr int NB_SPLIT = kFwdNbSplit;
-  static constexpr int NB = D == 64 ? kFwdNb64 : kFwdNb128;
-};
-template <int D> struct BwdCfg {
-  static constexpr int NB = D == 64 ? kBwdNb64 : kBwdNb128;
-};
+// Parts a work group's four waves split the other axis into.  A split work
+// group owns 64 (two parts) or 32 (four) rows instead of 128, so that a grid
+// of few work groups fills the GPU and its heaviest wave's run over the other
+// axis is a half or a quarter as long; the price is as many rings to copy and
+// LDS for them.  It pays while all work groups are resident from the start:
+// two per CU (forward at D = 64 in two parts: three; D = 128 in four: one).
+// Measured, unsplit / 2 / 4 parts, forward + dQ + dK/dV, us:
+//   D = 64:  B1 H12 S777 48 / 35 / 28, B1 H16 S1024 56 / 38 / 32 (512 work groups in four
+//            parts), B2 H12 S700 43 / 33 / 34 (528), B8 H12 S512 38 / 45 / 60
+//   D = 128: B1 H8 S512 55 / 40 / 31, B1 H2 S4096 313 / 190 / 127 (256 in four),
+//            B1 H24 S1024 96 / 67 / 96, B1 H16 S2048 172 / 122 / 177 (512 in two),
+//            B8 H16 S512 76 / 91 (1024 in two)
+static int split_parts(int D, int BH, int S, int64_t max2) {
+  const int cus = cu_count();
+  if ((int64_t)BH * ((S + 31) / 32) <= (D == 64 ? 2 : 1) * (int64_t)cus) return 4;
+  return (int64_t)BH * ((S + 63) / 64) <= max2 ? 2 : 1;
+}
+static int fwd_split(int D, int BH, int S) {
+  return split_parts(D, BH, S, (D == 64 ? 3 : 2) * (int64_t)cu_count());
+}
+// At D = 64 up to an eighth more than resident: B3 H12 S1024 (576 in two parts) dQ + dK/dV 42 / 33 us,
+// B8 H10 S512 not causal (640) 37.4 / 38.7, B8 H12 S512 (768) 28 / 35.
+static int bwd_split(int D, int BH, int S) {
+  return split_parts(D, BH, S, (D == 64 ? 9 * (int64_t)cu_count() / 4 : 2 * (int64_t)cu_count()));
+}
+
+// Ring depths per part (LDS slots of 32-row tiles): two slots where more would
+// leave room for only one work group per CU.
+template <int D, int SPLIT> constexpr int fwd_nb() {
+  return SPLIT == 1 ? (D == 64 ? kFwdNb64 : kFwdNb128) : D == 64 && SPLIT == 2 ? kFwdNbSplit : 2;
+}
+template <int D, int SPLIT> constexpr int bwd_nb() {
+  return SPLIT == 1 ? (D == 64 ? kBwdNb64 : kBwdNb128) : D == 64 && SPLIT == 2 ? kBwdNbSplit : 2;
+}
 
 template <int D, bool CAUSAL, int SPLIT, int NB, bool RAG, bool STR>
 static hipError_t launch_dq_t(const BwdArgs& a, float c, int n_qtiles, hipStream_t st) {
@@ -987,9 +1010,9 @@ static hipError_t launch_dkdv(const BwdArgs& a, float c, hipStream_t st) {
   constexpr int BKV = 128 / SPLIT;
   const int n_ktiles = (a.S + BKV - 1) / BKV;
   // dealt in alternating directions only when every work group is resident
-  // from the start (three per CU)
-  const int band = dkdv_lean<D, CAUSAL, SPLIT, NB>() && (int64_t)a.BH * n_ktiles <= 3 * (int64_t)cu_count()
-                       ? cu_count() : 0;
+  // from the start (three per CU at D = 64 unsplit, else two)
+  const int per_cu = D == 64 && SPLIT == 1 ? 3 : 2;
+  const int band = (int64_t)a.BH * n_ktiles <= per_cu * (int64_t)cu_count() ? cu_count() : 0;
   hipLaunchKernelGGL((attn_bwd_dkdv_bf16_kernel<D, CAUSAL, SPLIT, NB, RAG>), dim3((unsigned)((int64_t)a.BH * n_ktiles)),
                      dim3(256), 0, st, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.dout,
                      (const float*)a.ws, (bf16*)a.dk, (bf16*)a.dv, a.S, a.BH, n_ktiles, c, a.scale,
@@ -1009,16 +1032,11 @@ static hipError_t launch_fwd_split(const FwdArgs& a, hipStream_t st) {
 
 template <int D, bool CAUSAL, bool RAG>
 static hipError_t fwd_bf16_t(const FwdArgs& a, hipStream_t st) {
-  if constexpr (D == 64) {
-    // Split each query tile's key range over two parts when the unsplit grid
-    // (128-query tiles) cannot fill the GPU's workgroup slots (three per CU).
-    // (The no-clamp test build never splits: a split part would then start on
-    // tiles that are fully masked for its queries, with no real score to set
-    // the softmax offset from.)
-    const bool split = !kNoClamp && (int64_t)a.BH * ((a.S + 127) / 128) < 3 * (int64_t)cu_count();
-    if (split) return launch_fwd_split<D, CAUSAL, 2, FwdCfg<D>::NB_SPLIT, RAG>(a, st);
+  switch (fwd_split(D, a.BH, a.S)) {
+    case 4: return launch_fwd_split<D, CAUSAL, 4, fwd_nb<D, 4>(), RAG>(a, st);
+    case 2: return launch_fwd_split<D, CAUSAL, 2, fwd_nb<D, 2>(), RAG>(a, st);
+    default: return launch_fwd_split<D, CAUSAL, 1, fwd_nb<D, 1>(), RAG>(a, st);
   }
-  return launch_fwd_split<D, CAUSAL, 1, FwdCfg<D>::NB, RAG>(a, st);
 }
 
 // The kernels come in two builds: with the ragged-end handling (S not a
@@ -1034,31 +1052,23 @@ hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t st) {
   return a.causal ? fwd_bf16_r<128, true>(a, st) : fwd_bf16_r<128, false>(a, st);
 }
 
-template <int D, bool CAUSAL, bool RAG>
-static hipError_t bwd_bf16_t(const BwdArgs& a, int phase, hipStream_t st) {
-  constexpr int NB = BwdCfg<D>::NB;
+template <int D, bool CAUSAL, bool RAG, int SPLIT>
+static hipError_t bwd_bf16_s(const BwdArgs& a, int phase, hipStream_t st) {
   const float c = a.scale * kLog2e;
-  // Split the key range of a query tile (dQ), or the query range of a key tile
-  // (dK/dV), over two parts when the unsplit grid cannot fill the GPU's
-  // workgroup slots (two per CU): the heaviest causal tile's sequential chain
-  // then sets the time.  With a full grid the unsplit kernels have less
-  // overhead per unit of work.
-  bool split = false;
-  if constexpr (D == 64)
-    split = !kNoClamp && (int64_t)a.BH * ((a.S + 127) / 128) < kBwdSplitWgPerCu * (int64_t)cu_count();
   if (phase != 2) {
-    hipError_t e;
-    if constexpr (D == 64) {
-      e = split ? launch_dq<D, CAUSAL, 2, kBwdNbSplit, RAG>(a, c, st) : launch_dq<D, CAUSAL, 1, NB, RAG>(a, c, st);
-    } else {
-      e = launch_dq<D, CAUSAL, 1, NB, RAG>(a, c, st);
-    }
+    hipError_t e = launch_dq<D, CAUSAL, SPLIT, bwd_nb<D, SPLIT>(), RAG>(a, c, st);
     if (e != hipSuccess || phase == 1) return e;
   }
-  if constexpr (D == 64) {
-    if (split) return launch_dkdv<D, CAUSAL, 2, kBwdNbSplit, RAG>(a, c, st);
+  return launch_dkdv<D, CAUSAL, SPLIT, bwd_nb<D, SPLIT>(), RAG>(a, c, st);
+}
+
+template <int D, bool CAUSAL, bool RAG>
+static hipError_t bwd_bf16_t(const BwdArgs& a, int phase, hipStream_t st) {
+  switch (bwd_split(D, a.BH, a.S)) {
+    case 4: return bwd_bf16_s<D, CAUSAL, RAG, 4>(a, phase, st);
+    case 2: return bwd_bf16_s<D, CAUSAL, RAG, 2>(a, phase, st);
+    default: return bwd_bf16_s<D, CAUSAL, RAG, 1>(a, phase, st);
   }
-  return launch_dkdv<D, CAUSAL, 1, BwdCfg<D>::NB, RAG>(a, c, st);
 }
 
 template <int D, bool CAUSAL>

@@ -154,6 +154,27 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
+// ---------------------------------------------------------------------------
+// A work group's four waves are G row groups times 4/G interleaved parts of
+// the reduced axis (wave w: group w % G, part w / G; tile t of the axis belongs
+// to part t % (4/G)).  The parts' accumulators meet in LDS.
+// ---------------------------------------------------------------------------
+// Partial accumulators: wave w's index group g of column block dt at
+// [w][dt][g][lane].  The parts of one row group are waves grp, grp + G, ...
+template <int D>
+__device__ __forceinline__ void put_partial(f32x4* area, int w, int lane, const f32x16 (&acc)[(D / 32)]) {
+#pragma unroll
+  for (int dt = 0; dt < (D / 32); ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      area[((w * (D / 32) + dt) * 4 + g) * 64 + lane] =
+          f32x4{acc[dt][4 * g], acc[dt][4 * g + 1], acc[dt][4 * g + 2], acc[dt][4 * g + 3]};
+}
+template <int D>
+__device__ __forceinline__ f32x4 get_partial(const f32x4* area, int w, int dt, int g, int lane) {
+  return area[((w * (D / 32) + dt) * 4 + g) * 64 + lane];
+}
+
 // Store 4 consecutive row elements (one accumulator run) converted to T.
 template <typename T> __device__ __forceinline__ void store4(T* dst, float a, float b, float c, float d);
 template <> __device__ __forceinline__ void store4<__bf16>(__bf16* dst, float a, float b, float c, float d) {

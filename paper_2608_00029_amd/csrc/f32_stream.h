@@ -191,21 +191,6 @@ template <int D, int G, int N_FIXED> constexpr int f32_lds_units() {
   return fixed > merge ? fixed : merge;
 }
 
-// Partial accumulators: wave w's index group g of column block dt at
-// [w][dt][g][lane].  The parts of one row group are waves grp, grp + G, ...
-template <int D>
-__device__ __forceinline__ void put_partial(f32x4* area, int w, int lane, const f32x16 (&acc)[F32Geom<D>::DT]) {
-#pragma unroll
-  for (int dt = 0; dt < F32Geom<D>::DT; ++dt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      area[((w * F32Geom<D>::DT + dt) * 4 + g) * 64 + lane] =
-          f32x4{acc[dt][4 * g], acc[dt][4 * g + 1], acc[dt][4 * g + 2], acc[dt][4 * g + 3]};
-}
-template <int D>
-__device__ __forceinline__ f32x4 get_partial(const f32x4* area, int w, int dt, int g, int lane) {
-  return area[((w * F32Geom<D>::DT + dt) * 4 + g) * 64 + lane];
-}
 // Sum of the parts' accumulators in part order, through `area`, times f, to
 // this lane's output row (if `valid`).  Each wave finishes its share of the
 // index groups.  Every wave of the work group calls it; the area may hold
