@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPLIT == 1 
 void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                                                             const bf16* __restrict__ V, bf16* __restrict__ O,
                                                             float* __restrict__ LSE, int S, int BH, int n_qtiles,
-                                                            float c, int band, int H, int seq_major) {
+                                                            float c, int order, int H, int seq_major) {
   typedef TileGeom<D> G;
   constexpr int QG = 4 / SPLIT, BQ = 32 * QG;
   constexpr int TILE = G::TILE, SET = 2 * TILE;
@@ -105,7 +105,7 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index: uniform, kept in an SGPR
   const int qg = w % QG, part = w / QG;
   int bh, qt;
-  tile_of_block_banded(blockIdx.x, BH, n_qtiles, CAUSAL, CAUSAL ? band : 0, bh, qt);
+  tile_of_block_ordered(blockIdx.x, BH, n_qtiles, CAUSAL, order, bh, qt);
   const Rows rw = rows_of(bh, H, S, D, seq_major);
   const int64_t base = rw.base;
   const int rs = rw.rs;
@@ -445,7 +445,7 @@ void attn_bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict_
                                                                const bf16* __restrict__ dO,
                                                                const float* __restrict__ LSE, bf16* __restrict__ dQ,
                                                                float* __restrict__ ws, int S, int BH, int n_qtiles,
-                                                               float c, float scale, int band, int H, int seq_major) {
+                                                               float c, float scale, int order, int H, int seq_major) {
   typedef TileGeom<D> G;
   constexpr int QG = 4 / SPLIT, BQ = 32 * QG;
   constexpr int TILE = G::TILE, SET = 2 * TILE;
@@ -458,7 +458,7 @@ void attn_bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict_
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index: uniform, kept in an SGPR
   const int qg = w % QG, part = w / QG;
   int bh, qt;
-  tile_of_block_banded(blockIdx.x, BH, n_qtiles, CAUSAL, CAUSAL ? band : 0, bh, qt);
+  tile_of_block_ordered(blockIdx.x, BH, n_qtiles, CAUSAL, order, bh, qt);
   const Rows rw = rows_of(bh, H, S, D, seq_major);
   const int64_t base = rw.base;
   const int rs = rw.rs;
@@ -684,7 +684,7 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
                                                                  const bf16* __restrict__ dO,
                                                                  const float* __restrict__ ws,
                                                                  bf16* __restrict__ dK, bf16* __restrict__ dV, int S,
-                                                                 int BH, int n_ktiles, float c, float scale, int band,
+                                                                 int BH, int n_ktiles, float c, float scale, int order,
                                                                  int H, int seq_major) {
   typedef TileGeom<D> G;
   constexpr bool LEAN = dkdv_lean<D, CAUSAL, SPLIT, NB>();
@@ -713,7 +713,7 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index: uniform, kept in an SGPR
   const int kg = w % KG, part = w / KG;
   int bh, kt;
-  tile_of_block_banded(blockIdx.x, BH, n_ktiles, false, CAUSAL ? band : 0, bh, kt);
+  tile_of_block_ordered(blockIdx.x, BH, n_ktiles, false, order, bh, kt);
   const Rows rw = rows_of(bh, H, S, D, seq_major);
   const int64_t base = rw.base;
   const int rs = rw.rs;
@@ -950,6 +950,22 @@ int cu_count() {
   return cached[dev];
 }
 
+// Work-group order of a grid of BH heads x n_tiles with per_cu work groups
+// resident per CU: `otherwise`, or kHeadGroup heads at a time where the grid
+// takes more than one round, there are at least three groups of heads and
+// sequences are short enough that a group's heads (eight per chiplet) stream
+// from its 4 MB L2.  Forward + dQ + dK/dV, over all heads / 64 at a time, us:
+// B16 H16 S512 D128 156 / 138, B16 H16 S1024 D128 432 / 401, B32 H16 S200 D128
+// 113 / 101, B32 H16 S512 D64 148 / 139, B16 H32 S1024 D64 417 / 406, B16 H16
+// S1024 D64 205 / 200; but B16 H12 S2048 D64 498 / 522 (its longest tiles then
+// start in every group's last round), B8 H16 S1024 D64 (two groups) 109 / 116,
+// and the forward of B16 H16 S512 D64 (resident at once) 19.5 / 22.4.
+constexpr int kHeadGroup = 64;
+static int work_order(int BH, int S, int n_tiles, int per_cu, int otherwise) {
+  return S <= 1024 && BH >= 3 * kHeadGroup && (int64_t)BH * n_tiles > per_cu * (int64_t)cu_count() ? -kHeadGroup
+                                                                                                   : otherwise;
+}
+
 // Parts a work group's four waves split the other axis into.  A split work
 // group owns 64 (two parts) or 32 (four) rows instead of 128, so that a grid
 // of few work groups fills the GPU and its heaviest wave's run over the other
@@ -990,7 +1006,9 @@ static hipError_t launch_dq_t(const BwdArgs& a, float c, int n_qtiles, hipStream
   hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, CAUSAL, SPLIT, NB, RAG, STR>),
                      dim3((unsigned)((int64_t)a.BH * n_qtiles)), dim3(256), 0, st, (const bf16*)a.q,
                      (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.o, (const bf16*)a.dout, a.lse, (bf16*)a.dq,
-                     a.ws, a.S, a.BH, n_qtiles, c, a.scale, cu_count(), a.H, (int)a.seq_major);
+                     a.ws, a.S, a.BH, n_qtiles, c, a.scale,
+                     work_order(a.BH, a.S, n_qtiles, D == 64 ? 4 : 2, CAUSAL ? cu_count() : 0), a.H,
+                     (int)a.seq_major);
   return hipGetLastError();
 }
 
@@ -1012,11 +1030,14 @@ static hipError_t launch_dkdv(const BwdArgs& a, float c, hipStream_t st) {
   // dealt in alternating directions only when every work group is resident
   // from the start (three per CU at D = 64 unsplit, else two)
   const int per_cu = D == 64 && SPLIT == 1 ? 3 : 2;
-  const int band = (int64_t)a.BH * n_ktiles <= per_cu * (int64_t)cu_count() ? cu_count() : 0;
+  const int band = CAUSAL && (int64_t)a.BH * n_ktiles <= per_cu * (int64_t)cu_count() ? cu_count() : 0;
+  // (heads in groups: not without the mask at D = 128, where every work group
+  // streams the whole head: B16 H16 S512 85 us over all heads, 86-104 in groups)
+  const int order = CAUSAL || D == 64 ? work_order(a.BH, a.S, n_ktiles, per_cu, band) : band;
   hipLaunchKernelGGL((attn_bwd_dkdv_bf16_kernel<D, CAUSAL, SPLIT, NB, RAG>), dim3((unsigned)((int64_t)a.BH * n_ktiles)),
                      dim3(256), 0, st, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.dout,
                      (const float*)a.ws, (bf16*)a.dk, (bf16*)a.dv, a.S, a.BH, n_ktiles, c, a.scale,
-                     band, a.H, (int)a.seq_major);
+                     order, a.H, (int)a.seq_major);
   return hipGetLastError();
 }
 
@@ -1026,7 +1047,9 @@ static hipError_t launch_fwd_split(const FwdArgs& a, hipStream_t st) {
   const int n_qtiles = (a.S + BQ - 1) / BQ;
   hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, CAUSAL, SPLIT, NB, RAG>), dim3((unsigned)((int64_t)a.BH * n_qtiles)),
                      dim3(256), 0, st, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (bf16*)a.o, a.lse, a.S,
-                     a.BH, n_qtiles, a.scale * kLog2e, cu_count(), a.H, (int)a.seq_major);
+                     a.BH, n_qtiles, a.scale * kLog2e,
+                     work_order(a.BH, a.S, n_qtiles, D == 64 ? 4 : 3, CAUSAL ? cu_count() : 0), a.H,
+                     (int)a.seq_major);
   return hipGetLastError();
 }
 

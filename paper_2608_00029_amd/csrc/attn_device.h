@@ -230,5 +230,17 @@ __device__ __forceinline__ void tile_of_block_banded(int bid, int BH, int ntiles
                                                      int& tile) {
   tile_of_block(banded_rank(bid, BH * ntiles, band), BH, ntiles, heavy_last, bh, tile);
 }
+// order > 0: banded by `order`; order < 0: -order heads at a time (grouped_rank);
+// 0: heaviest first over all heads.
+__device__ __forceinline__ void tile_of_block_ordered(int bid, int BH, int ntiles, bool heavy_last, int order, int& bh,
+                                                      int& tile) {
+  if (order < 0) {
+    const HeadRank hr = grouped_rank(bid, BH, ntiles, -order);
+    bh = hr.bh;
+    tile = heavy_last ? (ntiles - 1 - hr.rank) : hr.rank;
+  } else {
+    tile_of_block_banded(bid, BH, ntiles, heavy_last, order, bh, tile);
+  }
+}
 
 }  // namespace cattn

@@ -55,6 +55,22 @@ constexpr int banded_rank(int bid, int n, int band) {
   return r * band + (size / kXcdGroup - 1 - p / kXcdGroup) * kXcdGroup + p % kXcdGroup;
 }
 
+// Order of a grid of BH heads x ntiles tiles that is too large to be resident
+// at once: heads are taken hg at a time (the last group may be smaller), and
+// inside a group the ranks 0 .. ntiles-1 of all its heads are dealt rank by
+// rank.  Work groups that run together then share few enough heads for the
+// streamed operands of those on one chiplet to stay in its L2.  A permutation
+// of the heads' tiles for any hg >= 1; hg >= BH is the plain rank-by-rank order.
+struct HeadRank {
+  int bh, rank;
+};
+constexpr HeadRank grouped_rank(int bid, int BH, int ntiles, int hg) {
+  const int g = (int)(bid / ((long long)hg * ntiles));
+  const int rem = (int)(bid - (long long)g * hg * ntiles);
+  const int n = imin(hg, BH - g * hg);
+  return HeadRank{g * hg + rem % n, rem / n};
+}
+
 // Ring with one barrier per group of G iterations (one part; G divides the
 // ring depth NB): the prologue copies tiles 0 .. NB-G-1, and at the top of
 // iteration i (i % G == 0) the copies of tiles i+NB-G .. i+NB-1 are issued

@@ -1,6 +1,6 @@
 """The bf16 attention kernels on either side of the rules that split a work
 group's other axis into two or four parts, with parts that have one tile more
-than others, parts without a tile, and ragged ends: every output of sampled
+than others, parts without a tile, and ragged ends, and grids taken in groups of heads: every output of sampled
 heads against the float64 oracle, with the tolerances and per-element bounds of
 the parity tests."""
 
@@ -24,6 +24,8 @@ CASES = [
     (1, 9, 1000, 128, True),   # 288: two parts
     (2, 32, 500, 128, False),  # 512 in two parts (the most)
     (2, 33, 500, 128, True),   # unsplit, ragged
+    (13, 16, 650, 64, True),   # 208 heads: three groups of 64 and one of 16, all kernels
+    (12, 16, 300, 128, False),  # 192 heads in three groups
 ]
 
 
