@@ -22,7 +22,8 @@
 //    dy * xhat and dy over its rows for dgamma / dbeta, the four waves of a
 //    group add theirs in a fixed order through LDS into one partial row of the
 //    workspace, and a second kernel sums the partial rows column by column.
-//  * Cross-entropy forward: one work group per row; each lane keeps a running
+//  * Cross-entropy forward: one work group per row (of 16 waves where there
+//    are few, long rows); each lane keeps a running
 //    (maximum, sum of exponentials) in base 2 and the lanes are merged with
 //    the rescale-by-maximum-difference rule.  Mean loss: one work group.
 //  * Cross-entropy backward: a flat grid of 4096-entry row chunks;
@@ -259,21 +260,22 @@ __device__ __forceinline__ void merge_stats(float& m, float& s, float m2, float 
   m = mm;
 }
 
-__global__ __launch_bounds__(256) void sce_fwd_kernel(const float* __restrict__ z, const int* __restrict__ targets,
-                                                      float* __restrict__ lse, float* __restrict__ row_loss, int V) {
-  __shared__ float red[2][4];
+template <int NT>
+__global__ __launch_bounds__(NT) void sce_fwd_kernel(const float* __restrict__ z, const int* __restrict__ targets,
+                                                     float* __restrict__ lse, float* __restrict__ row_loss, int V) {
+  __shared__ float red[2][NT / 64];
   const int row = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const f32x4* zr = (const f32x4*)(z + (int64_t)row * V);
   const int V4 = V >> 2;
   float m = -INFINITY, s = 0.f;  // over z * log2(e)
-  for (int i0 = threadIdx.x; i0 < V4; i0 += 256 * kUnroll) {
+  for (int i0 = threadIdx.x; i0 < V4; i0 += NT * kUnroll) {
     f32x4 v[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u)
-      if (i0 + u * 256 < V4) v[u] = __builtin_nontemporal_load(&zr[i0 + u * 256]);
+      if (i0 + u * NT < V4) v[u] = __builtin_nontemporal_load(&zr[i0 + u * NT]);
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u)
-      if (i0 + u * 256 < V4) {
+      if (i0 + u * NT < V4) {
         const f32x4 a = v[u] * kLog2e;
         const float mx = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
         if (mx > m) {  // move the offset (rare once the row's large values are seen)
@@ -293,7 +295,7 @@ __global__ __launch_bounds__(256) void sce_fwd_kernel(const float* __restrict__ 
   if (threadIdx.x == 0) {
     m = red[0][0];
     s = red[1][0];
-    for (int i = 1; i < 4; ++i) merge_stats(m, s, red[0][i], red[1][i]);
+    for (int i = 1; i < NT / 64; ++i) merge_stats(m, s, red[0][i], red[1][i]);
     const float l = (m + log2f(s)) * kLn2;
     lse[row] = l;
     if (row_loss) {
@@ -418,8 +420,18 @@ hipError_t launch_gelu(const float* x, const float* dy, float* out, int64_t n, b
 
 hipError_t launch_sce_fwd(const float* z, const int* targets, float* lse, float* row_loss, int rows, int V,
                           hipStream_t st) {
-  hipLaunchKernelGGL(sce_fwd_kernel, dim3((unsigned)rows), dim3(256), 0, st, z, targets, lse,
-                     targets ? row_loss : nullptr, V);
+  // One work group per row.  With few rows (one per CU) of many entries the row
+  // is the parallelism: 16 waves a row keep four times the loads in flight.
+  // 256 / 1024 threads, us: 64 x 50304 16.4 / 9.5, 256 x 50304 17.7 / 12.5,
+  // 100 x 16380 8.2 / 7.1; but 512 x 50304 20.6 / 20.0, 1024 x 50304 35.8 /
+  // 35.2, and where 1024 threads' first loads already cover the row,
+  // 421 x 4164 6.0 / 7.3, 1024 x 8192 9.3 / 11.5.
+  if (rows <= 256 && V >= 4 * 1024 * kUnroll)
+    hipLaunchKernelGGL(sce_fwd_kernel<1024>, dim3((unsigned)rows), dim3(1024), 0, st, z, targets, lse,
+                       targets ? row_loss : nullptr, V);
+  else
+    hipLaunchKernelGGL(sce_fwd_kernel<256>, dim3((unsigned)rows), dim3(256), 0, st, z, targets, lse,
+                       targets ? row_loss : nullptr, V);
   return hipGetLastError();
 }
 
