@@ -255,7 +255,10 @@ __global__ __launch_bounds__(1024) void layernorm_bwd_reduce_kernel(const float*
 // the smaller side's sum is rescaled by 2^(its maximum - the larger maximum)).
 __device__ __forceinline__ void merge_stats(float& m, float& s, float m2, float s2) {
   const float mm = fmaxf(m, m2);
-  if (mm == -INFINITY) return;  // both sides empty
+  if (mm == -INFINITY) {  // nothing above -inf on either side: sums of 0, or NaN
+    s += s2;
+    return;
+  }
   s = s * exp2_hw(m - mm) + s2 * exp2_hw(m2 - mm);
   m = mm;
 }
@@ -282,7 +285,10 @@ __global__ __launch_bounds__(NT) void sce_fwd_kernel(const float* __restrict__ z
           s *= exp2_hw(m - mx);
           m = mx;
         }
-        s += (exp2_hw(a[0] - m) + exp2_hw(a[1] - m)) + (exp2_hw(a[2] - m) + exp2_hw(a[3] - m));
+        // before a lane's first logit above -inf there is no offset to subtract
+        // (-inf less -inf would be NaN, not an exponential of 0)
+        const float off = m == -INFINITY ? 0.f : m;
+        s += (exp2_hw(a[0] - off) + exp2_hw(a[1] - off)) + (exp2_hw(a[2] - off) + exp2_hw(a[3] - off));
       }
   }
 #pragma unroll
