@@ -746,18 +746,22 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
   const int w_diag = nt - 1 - kw / 32;
   const int i_diag = !CAUSAL || kw >= S ? -1 : kNoClamp ? (w_diag + SPLIT - 1 - part) / SPLIT
                      : w_diag % SPLIT == part ? w_diag / SPLIT : -1;
-  const int t_rag = RAG ? 0 : -1;                // walk position of the ragged (last) tile
-  const int i_rag = RAG && part == 0 ? 0 : -1;   // ... in this part
+  const int i_rag = RAG && part == 0 ? 0 : -1;   // iteration of the ragged (last) tile: walk position 0
 
   TileCopy<D> tc;
   tc.init(w, lane, rs);
-  auto dma = [&](int x, auto slc) {  // iteration x's tile of every part, into ring slot slc
+  // iteration x's tile of every part, into ring slot slc.  The ragged tile is
+  // the first of the walk, so only iteration 0's copies test for it: in the
+  // loop the test cost the two-part kernel at D = 128 its second work group
+  // per CU (262 registers against 256 now; B1 H16 S2040 without the mask 89 /
+  // 73 us, S2048 73).
+  auto dma_tiles = [&](int x, auto slc, auto rag) {
 #pragma unroll
     for (int p = 0; p < SPLIT; ++p) {
       const int t = SPLIT == 1 ? x : min(x * SPLIT + p, n - 1);  // (a part without a last tile copies another's)
       const int row0 = (nt - 1 - t) * 32;
       char* b = smem + (p * NB + decltype(slc)::value) * SETB;
-      if (!RAG || t != t_rag) {
+      if (!decltype(rag)::value || t != 0) {
         tc.copy_full(Qb, row0, b);
         tc.copy_full(dOb, row0, b + TILE);
       } else {
@@ -767,11 +771,13 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
       if (lane < 4) dma16(wsh + row0, ld_voff, lds_addr(smem + AUX0 + (p * NB + decltype(slc)::value) * AUX) + 64 * w);
     }
   };
+  auto dma = [&](int x, auto slc) { dma_tiles(x, slc, IC<0>{}); };
+  auto dma_first = [&](int x, auto slc) { dma_tiles(x, slc, IC<(RAG && decltype(slc)::value == 0)>{}); };
   constexpr int NEED = LEAN || STREAM ? 0 : 1;  // iteration i reads the tiles of iterations i .. i+NEED
   // With one part, the waves meet at a barrier every GROUP iterations: a wave
   // that runs late on its SIMD then holds the others back less often.
   constexpr int GROUP = ring_group(SPLIT, NB, NEED, kDkdvGroup);
-  ring_prologue<NB, GROUP>(L, dma);
+  ring_prologue<NB, GROUP>(L, dma_first);
   MB::frag kf[KS_D], vf[KS_D];
   load_row_frags<bf16, D>(K + base, my_k, S, h, rs, kf);
   load_row_frags<bf16, D>(V + base, my_k, S, h, rs, vf);
@@ -914,7 +920,11 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
 
   if constexpr (SPLIT > 1) {
     wait_vm(0);  // the rings' last copies; then every wave adds its share of the parts
-    const int64_t row = base + (int64_t)my_k * rs;
+    // (through an opaque copy: kept from the K row's load, the offset would
+    // occupy two registers across the loop)
+    int key = my_k;
+    asm volatile("" : "+v"(key));
+    const int64_t row = base + (int64_t)key * rs;
     sum_parts_and_store<D, KG>((f32x4*)smem, w, h, lane, dkacc, dK + row, my_k < S, scale);
     sum_parts_and_store<D, KG>((f32x4*)smem, w, h, lane, dvacc, dV + row, my_k < S, 1.f);
     return;
