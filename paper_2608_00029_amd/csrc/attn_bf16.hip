@@ -976,34 +976,9 @@ static int work_order(int BH, int S, int n_tiles, int per_cu, int otherwise) {
                                                                                                    : otherwise;
 }
 
-// Parts a work group's four waves split the other axis into.  A split work
-// group owns 64 (two parts) or 32 (four) rows instead of 128, so that a grid
-// of few work groups fills the GPU and its heaviest wave's run over the other
-// axis is a half or a quarter as long; the price is as many rings to copy and
-// LDS for them.  It pays while all work groups are resident from the start:
-// two per CU (forward at D = 64 in two parts: three; D = 128 in four: one).
-// Measured, unsplit / 2 / 4 parts, forward + dQ + dK/dV, us:
-//   D = 64:  B1 H12 S777 48 / 35 / 28, B1 H16 S1024 56 / 38 / 32 (512 work groups in four
-//            parts), B2 H12 S700 43 / 33 / 34 (528), B8 H12 S512 38 / 45 / 60
-//   D = 128: B1 H8 S512 55 / 40 / 31, B1 H2 S4096 313 / 190 / 127 (256 in four),
-//            B1 H24 S1024 96 / 67 / 96, B1 H16 S2048 172 / 122 / 177 (512 in two),
-//            B8 H16 S512 76 / 91 (1024 in two)
-static int split_parts(int D, int BH, int S, int64_t max2) {
-  const int cus = cu_count();
-  if ((int64_t)BH * ((S + 31) / 32) <= (D == 64 ? 2 : 1) * (int64_t)cus) return 4;
-  return (int64_t)BH * ((S + 63) / 64) <= max2 ? 2 : 1;
-}
-static int fwd_split(int D, int BH, int S) {
-  return split_parts(D, BH, S, (D == 64 ? 3 : 2) * (int64_t)cu_count());
-}
-// At D = 64 up to an eighth more than resident: B3 H12 S1024 (576 in two parts) dQ + dK/dV 42 / 33 us,
-// B8 H10 S512 not causal (640) 37.4 / 38.7, B8 H12 S512 (768) 28 / 35.
-static int bwd_split(int D, int BH, int S) {
-  return split_parts(D, BH, S, (D == 64 ? 9 * (int64_t)cu_count() / 4 : 2 * (int64_t)cu_count()));
-}
-
-// Ring depths per part (LDS slots of 32-row tiles): two slots where more would
-// leave room for only one work group per CU.
+// Ring depths per part (LDS slots of 32-row tiles): in four parts, and in two
+// at D = 128, two slots (64 KB of rings a work group, two per CU; four parts at
+// D = 128 128 KB, one).
 template <int D, int SPLIT> constexpr int fwd_nb() {
   return SPLIT == 1 ? (D == 64 ? kFwdNb64 : kFwdNb128) : D == 64 && SPLIT == 2 ? kFwdNbSplit : 2;
 }
@@ -1065,7 +1040,7 @@ static hipError_t launch_fwd_split(const FwdArgs& a, hipStream_t st) {
 
 template <int D, bool CAUSAL, bool RAG>
 static hipError_t fwd_bf16_t(const FwdArgs& a, hipStream_t st) {
-  switch (fwd_split(D, a.BH, a.S)) {
+  switch (split_parts(Pass::kFwd, D, CAUSAL, a.BH, a.S, cu_count())) {
     case 4: return launch_fwd_split<D, CAUSAL, 4, fwd_nb<D, 4>(), RAG>(a, st);
     case 2: return launch_fwd_split<D, CAUSAL, 2, fwd_nb<D, 2>(), RAG>(a, st);
     default: return launch_fwd_split<D, CAUSAL, 1, fwd_nb<D, 1>(), RAG>(a, st);
@@ -1085,23 +1060,32 @@ hipError_t launch_fwd_bf16(const FwdArgs& a, hipStream_t st) {
   return a.causal ? fwd_bf16_r<128, true>(a, st) : fwd_bf16_r<128, false>(a, st);
 }
 
-template <int D, bool CAUSAL, bool RAG, int SPLIT>
-static hipError_t bwd_bf16_s(const BwdArgs& a, int phase, hipStream_t st) {
-  const float c = a.scale * kLog2e;
-  if (phase != 2) {
-    hipError_t e = launch_dq<D, CAUSAL, SPLIT, bwd_nb<D, SPLIT>(), RAG>(a, c, st);
-    if (e != hipSuccess || phase == 1) return e;
+template <int D, bool CAUSAL, bool RAG>
+static hipError_t dq_bf16_t(const BwdArgs& a, float c, hipStream_t st) {
+  switch (split_parts(Pass::kDq, D, CAUSAL, a.BH, a.S, cu_count())) {
+    case 4: return launch_dq<D, CAUSAL, 4, bwd_nb<D, 4>(), RAG>(a, c, st);
+    case 2: return launch_dq<D, CAUSAL, 2, bwd_nb<D, 2>(), RAG>(a, c, st);
+    default: return launch_dq<D, CAUSAL, 1, bwd_nb<D, 1>(), RAG>(a, c, st);
   }
-  return launch_dkdv<D, CAUSAL, SPLIT, bwd_nb<D, SPLIT>(), RAG>(a, c, st);
+}
+
+template <int D, bool CAUSAL, bool RAG>
+static hipError_t dkdv_bf16_t(const BwdArgs& a, float c, hipStream_t st) {
+  switch (split_parts(Pass::kDkdv, D, CAUSAL, a.BH, a.S, cu_count())) {
+    case 4: return launch_dkdv<D, CAUSAL, 4, bwd_nb<D, 4>(), RAG>(a, c, st);
+    case 2: return launch_dkdv<D, CAUSAL, 2, bwd_nb<D, 2>(), RAG>(a, c, st);
+    default: return launch_dkdv<D, CAUSAL, 1, bwd_nb<D, 1>(), RAG>(a, c, st);
+  }
 }
 
 template <int D, bool CAUSAL, bool RAG>
 static hipError_t bwd_bf16_t(const BwdArgs& a, int phase, hipStream_t st) {
-  switch (bwd_split(D, a.BH, a.S)) {
-    case 4: return bwd_bf16_s<D, CAUSAL, RAG, 4>(a, phase, st);
-    case 2: return bwd_bf16_s<D, CAUSAL, RAG, 2>(a, phase, st);
-    default: return bwd_bf16_s<D, CAUSAL, RAG, 1>(a, phase, st);
+  const float c = a.scale * kLog2e;
+  if (phase != 2) {
+    hipError_t e = dq_bf16_t<D, CAUSAL, RAG>(a, c, st);
+    if (e != hipSuccess || phase == 1) return e;
   }
+  return dkdv_bf16_t<D, CAUSAL, RAG>(a, c, st);
 }
 
 template <int D, bool CAUSAL>

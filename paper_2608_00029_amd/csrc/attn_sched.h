@@ -30,6 +30,63 @@ constexpr int ring_in_flight(int i, int L, int n_last, int split, int ahead, int
 // (i + ahead - 1 < n_last): a compile-time count.
 constexpr int ring_in_flight_full(int split, int ahead, int need) { return (ahead - 1 - need) * split; }
 
+// The bf16 attention kernels: forward, dQ, dK/dV.
+enum class Pass { kFwd, kDq, kDkdv };
+
+// Parts (1, 2 or 4) that a bf16 work group's four waves split the other axis
+// into.  A split work group owns 64 (two parts) or 32 (four) rows instead of
+// 128, so that a grid of few work groups fills the GPU and its heaviest wave's
+// run over the other axis is a half or a quarter as long; the price is as many
+// rings to copy, the LDS for them and the parts' merge.  What decides is
+//  * the tiles to share, nt: with one or two a part has none or one, and the
+//    merge costs more than the run it shortens;
+//  * 32-row groups per CU, g = BH nt / CUs: up to 1 (2 at D = 64) the four-part
+//    work groups are resident from the start, up to 4 the two-part ones (LDS,
+//    registers);
+//  * with the mask, nt again: a long sequence's heaviest tile runs alone at the
+//    end of the grid, so the shorter run pays even where work groups queue.
+// Measured, unsplit / two / four parts, us (F forward, Q dQ, K dK/dV; c causal):
+//   few tiles  c S64 D64, g 1: F 4.2 / 4.6 / 4.6, K 4.9 / 5.6 / 5.5; c S128 D64, g 1: F 5.2 / 5.1 / 4.7,
+//              K 6.8 / 6.2 / 5.5, g 2: F 5.3 / 5.3 / 5.7, K 7.0 / 6.5 / 7.5; c S384 D64, g 1.5: K - / 8.8 / 7.7
+//   four, two  S256 D64, g 2: F 7.1 / 6.0 / 5.8, Q 8.3 / 7.0 / 8.0; c S512 D64, g 2: Q 10.8 / 8.9 / 8.7;
+//              S1024 D64, g 2: Q 17.8 / 12.9 / 12.9; c S2048 D64, g 3: F 28.5 / 18.1 / 16.9,
+//              K 41.6 / 25.8 / 25.1; S2048 D64, g 3: F 27.9 / 23.0 / 24.5; c S128 D128, g 2: F 7.9 / 7.0 / 10.7
+//   two, none  c S512 D64, g 4: F 10.2 / 8.3, Q 12.1 / 11.2, K 14.5 / 12.4; c S1024 D64, g 6: F 16.9 / 13.6,
+//              Q 18.2 / 19.9, K 24.4 / 23.9, g 7: F 17.4 / 16.4, K 24.5 / 26.1; c S4096 D64, g 9: F 57.8 / 54.2,
+//              g 7: Q 59.4 / 58.2, K 82.4 / 68.7; S2048 D64, g 6: F 38.2 / 33.7, Q 45.8 / 45.8, K 61.2 / 57.7,
+//              g 7: F 40.1 / 43.3, K 64.5 / 69.3; c S256 D128, g 3: F 10.7 / 9.4, Q 13.7 / 13.6, K 16.6 / 15.0;
+//              S256 D128, g 3: F 11.1 / 11.6, Q 14.5 / 16.1; S512 D128, g 4: F 16.7 / 16.8, Q 21.4 / 22.9,
+//              K 36.9 / 26.5; S2048 D128, g 5: F 59.1 / 61.5, K 102 / 105
+constexpr int split_parts(Pass pass, int D, bool causal, int BH, int S, int cus) {
+  const int nt = (S + 31) / 32;
+  if (nt < 3) return 1;
+  int four = 1, two = 2;  // largest g of each
+  if (D == 128) {
+    if (nt >= (causal ? 8 : 16)) two = 4;
+    if (causal && pass == Pass::kFwd && nt >= 4 && nt < 8) two = 3;
+  } else if (pass == Pass::kFwd) {
+    if (nt >= (causal ? 8 : 16)) four = 2;
+    if (causal && nt >= 8) two = 4;
+    if (nt >= 10) two = 6;
+    if (causal && nt >= 32) two = nt >= 128 ? 10 : nt >= 64 ? 9 : 7;
+  } else if (pass == Pass::kDq) {
+    if (nt >= (causal ? 16 : 32)) four = 2;
+    if (nt >= 16) two = 4;
+    if (causal && nt >= 32) two = nt >= 112 ? 8 : nt >= 40 ? 6 : 5;
+  } else {
+    if (nt >= (causal ? 8 : 32)) four = 2;
+    if (causal && nt >= 6) two = 3;
+    if (nt >= (causal ? 8 : 16)) two = 4;
+    if (nt >= 24) two = causal && nt >= 64 ? 8 : 6;
+  }
+  if (D == 64 && causal && nt >= 48) four = 3;
+  const long long g32 = (long long)BH * nt, g64 = (long long)BH * ((S + 63) / 64);
+  if (g32 <= (long long)four * cus) return 4;
+  // (an odd tile over: up to an eighth more 64-row groups than CUs is no loss yet)
+  if (two == 2 && nt >= 8) return g32 <= 2LL * cus ? 2 : 1;
+  return 2 * g64 <= (long long)two * cus ? 2 : 1;
+}
+
 // Order in which a grid of n work groups takes the work items, when items are
 // ranked heaviest first (rank 0 = most work).  Work groups are placed on the
 // GPU in rounds of `band` (one per compute unit): group b shares its compute

@@ -24,6 +24,10 @@ CASES = [
     (1, 9, 1000, 128, True),   # 288: two parts
     (2, 32, 500, 128, False),  # 512 in two parts (the most)
     (2, 33, 500, 128, True),   # unsplit, ragged
+    (4, 12, 1000, 64, True),   # forward and dK/dV in two parts, dQ unsplit
+    (2, 8, 1536, 64, True),    # four parts at three work groups per CU
+    (16, 20, 60, 64, True),    # two tiles: unsplit, ragged
+    (3, 40, 100, 128, False),  # four tiles, two parts, last tile of four rows
     (13, 16, 650, 64, True),   # 208 heads: three groups of 64 and one of 16, all kernels
     (12, 16, 300, 128, False),  # 192 heads in three groups
 ]
