@@ -1008,7 +1008,8 @@ static hipError_t launch_dq_t(const BwdArgs& a, float c, int n_qtiles, hipStream
                      dim3((unsigned)((int64_t)a.BH * n_qtiles)), dim3(256), 0, st, (const bf16*)a.q,
                      (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.o, (const bf16*)a.dout, a.lse, (bf16*)a.dq,
                      a.ws, a.S, a.BH, n_qtiles, c, a.scale,
-                     work_order(a.BH, a.S, n_qtiles, D == 64 ? 4 : 2, CAUSAL ? cu_count() : 0), a.H,
+                     work_order(a.BH, a.S, n_qtiles, D == 64 ? 4 : 2, CAUSAL ? query_band((int64_t)a.BH * n_qtiles, SPLIT, a.S, cu_count()) : 0),
+                     a.H,
                      (int)a.seq_major);
   return hipGetLastError();
 }
@@ -1029,9 +1030,11 @@ static hipError_t launch_dkdv(const BwdArgs& a, float c, hipStream_t st) {
   constexpr int BKV = 128 / SPLIT;
   const int n_ktiles = (a.S + BKV - 1) / BKV;
   // dealt in alternating directions only when every work group is resident
-  // from the start (three per CU at D = 64 unsplit, else two)
+  // from the start (three per CU at D = 64 unsplit, else two), in two or three
+  // rounds
   const int per_cu = D == 64 && SPLIT == 1 ? 3 : 2;
-  const int band = CAUSAL && (int64_t)a.BH * n_ktiles <= per_cu * (int64_t)cu_count() ? cu_count() : 0;
+  const int64_t n = (int64_t)a.BH * n_ktiles, cus = cu_count();
+  const int band = CAUSAL && n > cus && n <= per_cu * cus ? (int)cus : 0;
   // (heads in groups: not without the mask at D = 128, where every work group
   // streams the whole head: B16 H16 S512 85 us over all heads, 86-104 in groups)
   const int order = CAUSAL || D == 64 ? work_order(a.BH, a.S, n_ktiles, per_cu, band) : band;
@@ -1049,7 +1052,8 @@ static hipError_t launch_fwd_split(const FwdArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, CAUSAL, SPLIT, NB, RAG>), dim3((unsigned)((int64_t)a.BH * n_qtiles)),
                      dim3(256), 0, st, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (bf16*)a.o, a.lse, a.S,
                      a.BH, n_qtiles, a.scale * kLog2e,
-                     work_order(a.BH, a.S, n_qtiles, D == 64 ? 4 : 3, CAUSAL ? cu_count() : 0), a.H,
+                     work_order(a.BH, a.S, n_qtiles, D == 64 ? 4 : 3, CAUSAL ? query_band((int64_t)a.BH * n_qtiles, SPLIT, a.S, cu_count()) : 0),
+                     a.H,
                      (int)a.seq_major);
   return hipGetLastError();
 }

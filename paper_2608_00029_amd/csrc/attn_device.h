@@ -227,11 +227,12 @@ __device__ __forceinline__ void tile_of_block(int bid, int BH, int ntiles, bool 
 // in alternating directions (banded_rank), so that the work groups sharing a
 // compute unit carry complementary amounts of causal work.
 __device__ __forceinline__ void tile_of_block_banded(int bid, int BH, int ntiles, bool heavy_last, int band, int& bh,
-                                                     int& tile) {
-  tile_of_block(banded_rank(bid, BH * ntiles, band), BH, ntiles, heavy_last, bh, tile);
+                                                     int& tile, bool pair_up = true) {
+  tile_of_block(banded_rank(bid, BH * ntiles, band, pair_up), BH, ntiles, heavy_last, bh, tile);
 }
-// order > 0: banded by `order`; order < 0: -order heads at a time (grouped_rank);
-// 0: heaviest first over all heads.
+// order > 0: banded by `order` (kNoPairUp added: round 0 always forwards);
+// order < 0: -order heads at a time (grouped_rank); 0: heaviest first over all
+// heads.
 __device__ __forceinline__ void tile_of_block_ordered(int bid, int BH, int ntiles, bool heavy_last, int order, int& bh,
                                                       int& tile) {
   if (order < 0) {
@@ -239,7 +240,7 @@ __device__ __forceinline__ void tile_of_block_ordered(int bid, int BH, int ntile
     bh = hr.bh;
     tile = heavy_last ? (ntiles - 1 - hr.rank) : hr.rank;
   } else {
-    tile_of_block_banded(bid, BH, ntiles, heavy_last, order, bh, tile);
+    tile_of_block_banded(bid, BH, ntiles, heavy_last, order & (kNoPairUp - 1), bh, tile, order < kNoPairUp);
   }
 }
 

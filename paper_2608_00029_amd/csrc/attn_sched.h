@@ -92,24 +92,44 @@ constexpr int split_parts(Pass pass, int D, bool causal, int BH, int S, int cus)
 // GPU in rounds of `band` (one per compute unit): group b shares its compute
 // unit with groups b +- band, b +- 2 band, ...  Every other round walks the
 // ranks backwards, so that a compute unit that receives one of the heaviest
-// items in one round receives one of the lightest of the next; the last round,
-// which may be short and falls on the first units, always walks forwards, and
-// the rounds before it alternate up to it, so that the units it reaches are
-// those with the least before it.  The walk is
-// backwards in steps of kXcdGroup, keeping each rank's position within its
+// items in one round receives one of the lightest of the next.  Round 0 walks
+// forwards, except in a grid of two rounds (with `pair_up`): there it walks
+// backwards and the second round, which falls on the first units, forwards, so
+// that it reaches those with the least before it.  Over 800 shapes of one to
+// two rounds that was 0-20% faster than round 0 forwards (dQ, dK/dV; the
+// forward 0-8%); in grids of three to four rounds, where the last round starts
+// as units fall free, it was up to 14% slower (dQ, B1 H104 S1024 D128).  The
+// walk is backwards in steps of kXcdGroup, keeping each rank's position within its
 // group of kXcdGroup: work groups are dealt to the GPU's kXcdGroup chiplets
 // (each with its own L2) round-robin by index, and a rank keeps the chiplet of
 // the same-numbered group, so the tiles of one head, which share K/V or
 // Q/dO, stay in one L2.  band <= 0 keeps the plain heaviest-first order.  A
 // permutation of [0, n).
 constexpr int kXcdGroup = 8;
-constexpr int banded_rank(int bid, int n, int band) {
+constexpr int banded_rank(int bid, int n, int band, bool pair_up = true) {
   if (band <= 0) return bid;
-  const int r = bid / band, p = bid % band, last = (n - 1) / band;
-  if (((last - r) & 1) == 0) return bid;
+  const int r = bid / band, p = bid % band;
+  const int first_back = pair_up && n > band && n - band <= band ? 0 : 1;
+  if (((r - first_back) & 1) != 0) return bid;
   const int size = n - r * band < band ? n - r * band : band;
   if (size % kXcdGroup != 0 || band % kXcdGroup != 0) return r * band + size - 1 - p;
   return r * band + (size / kXcdGroup - 1 - p / kXcdGroup) * kXcdGroup + p % kXcdGroup;
+}
+
+// The `band` argument of the causal forward and dQ for a grid of n work groups
+// of 128/parts queries.  None for one round, where the order changes nothing
+// but costs its arithmetic (1-2% of the smallest grids), and none for a split
+// grid of over three rounds, which is not resident (forward, D = 64, two parts,
+// banded / plain: 3-8% slower).  kNoPairUp is added where the heaviest-first
+// ranks of a two-round grid are not heaviest first: the last of two or three
+// unsplit tiles, if of at most 96 queries, has the longest run but idle waves,
+// so less work than the tiles before it (forward, D = 128, paired up / round 0
+// forwards: B1 H205 S160 16% slower, B1 H171 S192 12%, B1 H128 S300 10%; four
+// tiles and more, whatever the last, 4-11% faster: B1 H80 S450 14.6 / 15.4 us).
+constexpr int kNoPairUp = 1 << 24;
+constexpr int query_band(long long n, int parts, int S, int cus) {
+  if (n <= cus || (parts > 1 && n > 3LL * cus)) return 0;
+  return cus + (parts == 1 && S < 384 && (S - 1) % 128 + 1 <= 96 ? kNoPairUp : 0);
 }
 
 // Order of a grid of BH heads x ntiles tiles that is too large to be resident

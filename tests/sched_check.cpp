@@ -44,19 +44,40 @@ int main() {
       }
     }
   }
-  // banded_rank is a permutation of [0, n) for every grid size and band
+  // banded_rank is a permutation of [0, n) for every grid size and band, with
+  // and without pairing up; only a grid of two rounds walks round 0 backwards
   for (int n = 1; n <= 1200; n += 7) {
     for (int band : {0, 1, 3, 80, 256, 304}) {
-      static unsigned char seen[1200];
-      for (int i = 0; i < n; ++i) seen[i] = 0;
-      for (int b = 0; b < n; ++b) {
-        ++checks;
-        const int r = banded_rank(b, n, band);
-        if (r < 0 || r >= n || seen[r]) ++bad;
-        else seen[r] = 1;
+      for (bool pair_up : {false, true}) {
+        static unsigned char seen[1200];
+        for (int i = 0; i < n; ++i) seen[i] = 0;
+        for (int b = 0; b < n; ++b) {
+          ++checks;
+          const int r = banded_rank(b, n, band, pair_up);
+          if (r < 0 || r >= n || seen[r]) ++bad;
+          else seen[r] = 1;
+          if (band == 0) continue;
+          // a unit's items: rounds alternate, so ranks within a round run one way or the other
+          const bool back = b + kXcdGroup < n && b / band == (b + kXcdGroup) / band &&
+                            banded_rank(b + kXcdGroup, n, band, pair_up) < r;
+          const bool two = n > band && n <= 2 * band;
+          if (band > kXcdGroup && b % band + kXcdGroup < band && b + kXcdGroup < n &&
+              back != ((b / band + (pair_up && two ? 1 : 0)) % 2 == 1))
+            ++bad;
+        }
       }
     }
   }
+  // the forward's and dQ's bands: none in one round or past three of a split
+  // grid, no pairing up behind a short last one of two or three unsplit tiles
+  for (int parts : {1, 2, 4})
+    for (int S : {32, 96, 97, 128, 160, 224, 225, 300, 384, 450, 1024})
+      for (long long n : {1LL, 256LL, 257LL, 512LL, 768LL, 769LL, 5000LL}) {
+        ++checks;
+        const bool short_last = S == 32 || S == 96 || S == 160 || S == 224 || S == 300;
+        const int want = n <= 256 || (parts > 1 && n > 768) ? 0 : 256 + (parts == 1 && short_last ? kNoPairUp : 0);
+        if (query_band(n, parts, S, 256) != want) ++bad;
+      }
   for (int S = 1; S <= 5000; ++S) {
     const int p = ws_rows(S);
     if (p % 32 != 0 || p < S || p >= S + 32) ++bad;
