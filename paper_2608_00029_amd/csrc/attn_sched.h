@@ -60,31 +60,37 @@ enum class Pass { kFwd, kDq, kDkdv };
 constexpr int split_parts(Pass pass, int D, bool causal, int BH, int S, int cus) {
   const int nt = (S + 31) / 32;
   if (nt < 3) return 1;
-  int four = 1, two = 2;  // largest g of each
+  // largest g of four parts, and twice that of two
+  int four = 1, two = 4;
   if (D == 128) {
-    if (nt >= (causal ? 8 : 16)) two = 4;
-    if (causal && pass == Pass::kFwd && nt >= 4 && nt < 8) two = 3;
+    if (nt >= (causal ? 8 : 16) || (causal && pass == Pass::kFwd && nt >= 4)) two = 8;
   } else if (pass == Pass::kFwd) {
     if (nt >= (causal ? 8 : 16)) four = 2;
-    if (causal && nt >= 8) two = 4;
-    if (nt >= 10) two = 6;
-    if (causal && nt >= 32) two = nt >= 128 ? 10 : nt >= 64 ? 9 : 7;
+    if (causal && nt >= 8) two = 8;
+    if (nt >= 10) two = 12;
+    if (causal && nt >= 32) two = nt >= 128 ? 20 : nt >= 64 ? 18 : 14;
   } else if (pass == Pass::kDq) {
     if (nt >= (causal ? 16 : 32)) four = 2;
-    if (nt >= 16) two = 4;
-    if (causal && nt >= 32) two = nt >= 112 ? 8 : nt >= 40 ? 6 : 5;
+    if (causal && nt >= 12) two = 6;
+    if (nt >= 16) two = 8;
+    if (causal && nt >= 20) two = nt >= 112 ? 16 : nt >= 40 ? 12 : nt >= 32 ? 10 : 9;
   } else {
     if (nt >= (causal ? 8 : 32)) four = 2;
-    if (causal && nt >= 6) two = 3;
-    if (nt >= (causal ? 8 : 16)) two = 4;
-    if (nt >= 24) two = causal && nt >= 64 ? 8 : 6;
+    if (causal && nt >= 6) two = nt >= 12 ? 9 : nt >= 8 ? 8 : 6;
+    if (!causal && nt >= 16) two = 8;
+    if (nt >= 24) two = causal && nt >= 64 ? 16 : 12;
   }
   if (D == 64 && causal && nt >= 48) four = 3;
   const long long g32 = (long long)BH * nt, g64 = (long long)BH * ((S + 63) / 64);
   if (g32 <= (long long)four * cus) return 4;
   // (an odd tile over: up to an eighth more 64-row groups than CUs is no loss yet)
-  if (two == 2 && nt >= 8) return g32 <= 2LL * cus ? 2 : 1;
-  return 2 * g64 <= (long long)two * cus ? 2 : 1;
+  if (two == 4 && nt >= 8) return g32 <= 2LL * cus ? 2 : 1;
+  // (a short last tile can give an unsplit grid a third round where two parts need no fifth:
+  // forward without the mask, B1 H40 S1568 D64 40.2 / 35.1)
+  if (pass == Pass::kFwd && D == 64 && !causal && nt >= 12 && (long long)BH * ((S + 127) / 128) > 2LL * cus &&
+      g64 <= 4LL * cus)
+    return 2;
+  return 4 * g64 <= (long long)two * cus ? 2 : 1;
 }
 
 // Order in which a grid of n work groups takes the work items, when items are

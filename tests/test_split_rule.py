@@ -29,17 +29,20 @@ MEASURED = {
     (128, True, 256, 25): (1, 1, 1),
     # short sequences: four parts only while each CU has one work group of 32 rows
     (64, True, 64, 128): (4, 4, 4), (64, True, 128, 128): (2, 2, 2), (128, True, 64, 128): (4, 4, 4),
-    (128, True, 128, 128): (2, 2, 2), (64, True, 192, 100): (1, 1, 1), (128, True, 256, 100): (1, 1, 1),
+    (128, True, 128, 128): (2, 2, 2), (64, True, 192, 100): (1, 1, 1), (128, True, 256, 100): (2, 1, 1),
     # two work groups of 32 rows per CU
     (64, False, 64, 256): (2, 2, 2), (64, True, 32, 512): (4, 4, 4), (64, False, 32, 512): (4, 2, 2),
     (64, False, 16, 1024): (4, 4, 4), (64, True, 32, 384): (4, 2, 4), (64, False, 56, 288): (2, 2, 2),
-    (64, True, 89, 224): (1, 1, 2),
+    (64, True, 89, 224): (1, 1, 2), (64, True, 48, 384): (2, 2, 2), (64, True, 68, 450): (2, 1, 2),
+    (64, True, 40, 777): (2, 2, 2), (64, True, 49, 650): (2, 2, 2),
     # long causal sequences: more parts, on larger grids
     (64, True, 6, 4096): (4, 4, 4), (64, True, 12, 2048): (4, 4, 4), (64, False, 12, 2048): (2, 2, 2),
     (64, True, 12, 4096): (2, 2, 2), (64, True, 24, 2048): (2, 2, 2), (64, True, 40, 1024): (2, 2, 2),
     (64, True, 14, 4096): (2, 2, 2), (64, True, 18, 4096): (2, 1, 1), (64, False, 28, 2048): (1, 1, 1),
+    (64, False, 40, 1568): (2, 1, 1),
     (64, True, 56, 1024): (2, 1, 1),
     # head dimension 128
+    (128, True, 152, 160): (2, 1, 1),
     (128, True, 16, 2048): (2, 2, 2), (128, False, 16, 2040): (2, 2, 2), (128, False, 96, 256): (1, 1, 1),
     (128, False, 20, 2048): (1, 1, 1),
     # the headline and the long-context training shapes
