@@ -3,9 +3,9 @@ the loop bounds).  libcattn_noclamp.so is the same library with the bf16
 attention loops visiting every tile -- the forward and dQ loops running past
 the diagonal, the dK/dV loop starting at query tile 0 -- and masking the tiles
 past the diagonal entirely.  Its O, LSE, dQ, dK and dV equal the product
-library's value for value on grids that run the unsplit kernels in both
-(+0 and -0 compare equal: an added zero product may flip the sign of an exact
-zero)."""
+library's value for value, with the other axis whole, in two and in four parts
+(parts are interleaved, so a tile belongs to the same part in both; +0 and -0
+compare equal: an added zero product may flip the sign of an exact zero)."""
 
 import ctypes
 import os
@@ -22,15 +22,22 @@ pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 
-# grids that take the unsplit kernels in the product library too: head
-# dimension 128 always, head dimension 64 from 768 work groups of 128 queries
+# the number of parts is the same in all three kernels (test_split_rule.py checks it)
 CASES = [
     # B, H, S, D, sigma
-    (8, 12, 1024, 64, 1.0),   # GPT-2 small
-    (4, 24, 1000, 64, 1.0),   # ragged end
+    (8, 12, 1024, 64, 1.0),   # GPT-2 small: unsplit
+    (4, 24, 1000, 64, 1.0),   # unsplit, ragged end
     (4, 32, 1000, 64, 1.0),   # 1024 work groups: the dQ kernel's streamed four-wave form
-    (1, 2, 300, 128, 1.0),    # small grid, ragged end
-    (1, 2, 384, 128, 3.0),    # peaked softmax
+    (2, 12, 700, 64, 1.0),    # two parts, ragged end
+    (2, 12, 704, 64, 3.0),    # two parts, peaked softmax
+    (1, 2, 300, 64, 1.0),     # four parts, ragged end
+    (1, 2, 384, 64, 3.0),     # four parts, peaked softmax
+    (2, 33, 500, 128, 1.0),   # unsplit, ragged end
+    (2, 33, 512, 128, 3.0),   # unsplit, peaked softmax
+    (1, 9, 1000, 128, 1.0),   # two parts, ragged end
+    (1, 9, 1024, 128, 3.0),   # two parts, peaked softmax
+    (1, 2, 300, 128, 1.0),    # four parts, ragged end
+    (1, 2, 384, 128, 3.0),    # four parts, peaked softmax
 ]
 
 

@@ -9,6 +9,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_noclamp import CASES as NOCLAMP_CASES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
@@ -75,6 +77,16 @@ def test_measured_limits(parts):
     want = [w for row in MEASURED.values() for w in row]
     wrong = [(s, g, w) for s, g, w in zip(shapes, parts(shapes), want) if g != w]
     assert not wrong, wrong
+
+
+def test_noclamp_cases_reach_every_form(parts):
+    """The comparison with the unclamped build runs every number of parts at both
+    head dimensions, with whole and with ragged tiles, in all three kernels."""
+    shapes = [(p, D, 1, B * H, S) for B, H, S, D, _ in NOCLAMP_CASES for p in (FWD, DQ, DKDV)]
+    got = parts(shapes)
+    assert all(len(set(got[i:i + 3])) == 1 for i in range(0, len(got), 3))
+    reached = {(D, n, S % 32 == 0) for (_, D, _, _, S), n in zip(shapes, got)}
+    assert reached == {(D, n, whole) for D in (64, 128) for n in (1, 2, 4) for whole in (True, False)}
 
 
 def test_range(parts):
