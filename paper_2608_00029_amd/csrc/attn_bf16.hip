@@ -234,7 +234,7 @@ void attn_fwd_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K
       constexpr int pc = PAR ? (sl & 1) : 0, pn = PAR ? (pc ^ 1) : 1;
       const int i = i0 + sl;
       if (i >= L) return;
-      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, L, dma);
+      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, dma);
       if (i >= cnt) return;  // wave-uniform: this wave is done, it only keeps the barriers
       if constexpr (LEANF) {
         const char* kt = ring + sl * SET;
@@ -564,7 +564,7 @@ void attn_bwd_dq_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict_
       constexpr int sl = decltype(slc)::value;
       const int i = i0 + sl;
       if (i >= L) return;
-      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, L, dma);
+      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, dma);
       if (i >= cnt) return;  // wave-uniform: this wave is done, it only keeps the barriers
       const int j = i * SPLIT + part;  // key tile of this iteration
       const char* cur = ring + sl * SET;
@@ -819,7 +819,7 @@ void attn_bwd_dkdv_bf16_kernel(const bf16* __restrict__ Q,
       constexpr int sl = decltype(slc)::value, sn = (sl + 1) % NB;
       const int i = i0 + sl;
       if (i >= L) return;
-      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, L, dma);
+      ring_step<NB, GROUP, NEED, SPLIT, PER_TILE, sl>(i, L, dma);
       if (i >= cnt) return;  // wave-uniform: this wave is done, it only keeps the barriers
       const char* lq = ring + sl * SETB;
       const char* ldo = lq + TILE;

@@ -93,14 +93,14 @@ template <int N> __device__ __forceinline__ void tile_barrier_c() {
 // every wave issues PER_TILE copies per tile and part.  The tiles before the
 // loop come from ring_prologue.
 template <int NB, int GROUP, int NEED, int SPLIT, int PER_TILE, int SL, typename Dma>
-__device__ __forceinline__ void ring_step(int i, int L, int n_last, Dma& dma) {
+__device__ __forceinline__ void ring_step(int i, int L, Dma& dma) {
   constexpr int AH = NB - 1;
   if constexpr (GROUP == 1) {
     if (i > 0) {
-      if (i + AH - 1 < n_last) {
+      if (i + AH <= L) {
         tile_barrier_c<ring_in_flight_full(SPLIT, AH, NEED) * PER_TILE>();
       } else {
-        tile_barrier(ring_in_flight(i, L, n_last, SPLIT, AH, NEED) * PER_TILE);
+        tile_barrier(ring_in_flight(i, L, SPLIT, AH, NEED) * PER_TILE);
       }
     }
     if (i + AH < L) dma(i + AH, IC<(SL + AH) % NB>{});

@@ -1,5 +1,5 @@
 // Exhaustive check of the ring-schedule arithmetic of attn_sched.h against an
-// explicit simulation of the copies, for every ring depth, split and read
+// explicit simulation of the copies, for every ring depth, number of parts and read
 // depth the kernels use and every tile count up to 300.
 #include <cstdio>
 #include <initializer_list>
@@ -12,34 +12,45 @@ using namespace cattn;
 
 int main() {
   long bad = 0, checks = 0;
-  for (int NB : {3, 4, 6, 8}) {
+  // one barrier per iteration: n tiles dealt to the parts in turn, every part
+  // copying one per iteration, in issue order
+  for (int NB : {2, 3, 4, 6, 8}) {
     const int AH = NB - 1;
-    for (int split : {1, 2}) {
+    for (int split : {1, 2, 4}) {
       for (int need : {0, 1}) {
         if (need >= AH) continue;
         for (int n = 1; n <= 300; ++n) {
-          const int L = (n + split - 1) / split, n_last = n - (split - 1) * L;
-          auto tiles = [&](int x) { return (x < L ? split - 1 : 0) + (x < n_last ? 1 : 0); };
-          for (int i = 1; i < L; ++i) {
+          const int L = (n + split - 1) / split;
+          std::vector<int> order;  // iteration of every part tile, in issue order
+          auto copy = [&](int x) {
+            for (int p = 0; p < split; ++p) order.push_back(x);
+          };
+          for (int x = 0; x < AH && x < L; ++x) copy(x);  // before the loop, which waits for all of them
+          for (int i = 0; i < L; ++i) {
             ++checks;
-            // copies issued before the wait at the top of iteration i, in iteration order:
-            // iterations 0 .. AH-1 before the loop, iteration i'+AH at the top of iteration i' < i
-            int issued = 0;
-            for (int x = 0; x < L && x <= i - 1 + AH; ++x) issued += tiles(x);
-            const int f = ring_in_flight(i, L, n_last, split, AH, need);
-            int required = 0;  // every part tile this iteration reads
-            for (int x = 0; x <= i + need && x < L; ++x) required += tiles(x);
-            if (f < 0 || issued - f < required) ++bad;
-            if (i + AH - 1 < n_last && f != ring_in_flight_full(split, AH, need)) ++bad;
+            const int f = i == 0 ? 0 : ring_in_flight(i, L, split, AH, need);
+            if (f < 0 || f > (int)order.size()) {
+              ++bad;
+              continue;
+            }
+            // everything older than the newest f has landed: no tile read by iterations i .. i+need is among those
+            for (size_t x = order.size() - f; x < order.size(); ++x)
+              if (order[x] <= i + need) ++bad;
+            // ... and they have all been issued
+            for (int x = i; x <= i + need && x < L; ++x)
+              if (x > i - 1 + AH) ++bad;
+            if (i > 0 && i + AH <= L && f != ring_in_flight_full(split, AH, need)) ++bad;
             // the copy issued at the top of iteration i (iteration i+AH) reuses the buffer
             // of iteration i-1, finished before the barrier, never one read at i .. i+need
             if (i + AH < L) {
               const int b = (i + AH) % NB;
-              if (b != (i - 1) % NB) ++bad;
+              if (b != (i + NB - 1) % NB) ++bad;
               for (int k = 0; k <= need; ++k)
                 if (b == (i + k) % NB) ++bad;
+              copy(i + AH);
             }
           }
+          if ((int)order.size() != L * split) ++bad;  // every tile of every part was copied
         }
       }
     }
