@@ -255,11 +255,9 @@ __global__ __launch_bounds__(1024) void layernorm_bwd_reduce_kernel(const float*
 // the smaller side's sum is rescaled by 2^(its maximum - the larger maximum)).
 __device__ __forceinline__ void merge_stats(float& m, float& s, float m2, float s2) {
   const float mm = fmaxf(m, m2);
-  if (mm == -INFINITY) {  // nothing above -inf on either side: sums of 0, or NaN
-    s += s2;
-    return;
-  }
-  s = s * exp2_hw(m - mm) + s2 * exp2_hw(m2 - mm);
+  // nothing above -inf on either side: sums of 0, or NaN, and no offset to subtract
+  const float off = mm == -INFINITY ? 0.f : mm;
+  s = s * exp2_hw(m - off) + s2 * exp2_hw(m2 - off);
   m = mm;
 }
 
