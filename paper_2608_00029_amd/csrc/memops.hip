@@ -31,6 +31,7 @@
 #include <math.h>
 
 #include "attn_device.h"
+#include "attn_launch.h"
 #include "memops_launch.h"
 
 namespace cattn {
@@ -424,13 +425,15 @@ hipError_t launch_gelu(const float* x, const float* dy, float* out, int64_t n, b
 
 hipError_t launch_sce_fwd(const float* z, const int* targets, float* lse, float* row_loss, int rows, int V,
                           hipStream_t st) {
-  // One work group per row.  With few rows (one per CU) of many entries the row
-  // is the parallelism: 16 waves a row keep four times the loads in flight.
-  // 256 / 1024 threads, us: 64 x 50304 16.4 / 9.5, 256 x 50304 17.7 / 12.5,
-  // 100 x 16380 8.2 / 7.1; but 512 x 50304 20.6 / 20.0, 1024 x 50304 35.8 /
-  // 35.2, and where 1024 threads' first loads already cover the row,
-  // 421 x 4164 6.0 / 7.3, 1024 x 8192 9.3 / 11.5.
-  if (rows <= 256 && V >= 4 * 1024 * kUnroll)
+  // One work group per row.  With few rows (at most one per CU) of many entries
+  // the row is the parallelism: 16 waves a row keep four times the loads in
+  // flight, which pays where 256 threads would take more than three rounds of
+  // them.  256 / 1024 threads, us (with the mean loss): 64 x 12288 6.1 / 6.2, 256 x 12288
+  // 6.3 / 6.4, 64 x 14336 6.5 / 6.3, 256 x 14336 6.7 / 6.6, 256 x 16380 8.4 /
+  // 7.4, 64 x 50304 14.1 / 8.9, 256 x 50304 17.4 / 10.7; 256 x 4096 5.3 / 5.8,
+  // 256 x 8192 5.8 / 6.1.  With two rows per CU 512 x 12288 7.7 / 8.1, 512 x
+  // 20000 10.2 / 9.9.
+  if (rows <= cu_count() && V > 3 * 256 * 4 * kUnroll)
     hipLaunchKernelGGL(sce_fwd_kernel<1024>, dim3((unsigned)rows), dim3(1024), 0, st, z, targets, lse,
                        targets ? row_loss : nullptr, V);
   else

@@ -16,7 +16,8 @@ from test_gpu_memops import _check_sce_rows
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows,V", [(1, 16384), (256, 16384), (257, 16384), (256, 16380), (3, 50304), (2, 16388)])
+@pytest.mark.parametrize("rows,V", [(1, 16384), (256, 16384), (257, 16384), (256, 16380), (3, 50304), (2, 16388),
+                                    (1, 12288), (1, 12292), (256, 12288), (256, 12292), (257, 12292)])
 def test_sce_row_rule(cuda, rows, V):
     z, t = make_sce_inputs(rows, V, seed=rows + V, sigma=3.0)
     say(f"sce rows={rows} V={V}")
