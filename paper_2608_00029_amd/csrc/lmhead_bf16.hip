@@ -125,7 +125,10 @@ __global__ __launch_bounds__(512) void lmhead_logits_stats_kernel(const bf16* __
   constexpr int SLOT = 16 * BLK;         // W: 8 blocks (256 rows), X: 8 blocks (256 rows)
   constexpr int NSLOT = 4;               // chunk c + 3 is copied while chunk c computes
   constexpr int COPIES = 4;              // per wave and chunk
-  constexpr int STORES = 34;             // per active wave and tile: 32 of logits, 2 of partials
+  // Stores per active wave and tile: 32 of logits, 2 of partials.  The waits
+  // below count on the compiler emitting no fewer: a merged store would let a
+  // chunk be read before it has landed (one more would only wait longer).
+  constexpr int STORES = 34;
   __shared__ __attribute__((aligned(16))) char smem[NSLOT * SLOT];
 
   const int n_vt = lmh_vtiles(N), n_mt = lmh_mtiles(M);

@@ -1,8 +1,9 @@
 """The loss head at the edges of its copy ring and of the merge: work groups
 that walk several tiles with only two chunks of K per tile (stores of one tile
 in flight over all chunks of the next), waves past the end of a ragged last
-tile among them, tiles cut into parts for the last round, and rows of more and of exactly as many partials as the merge
-holds in registers.  Every output of sampled rows against the float64 oracle,
+tile among them, tiles cut into parts for the last round, work groups with more
+items than they look up at once, and rows of more and of exactly as many
+partials as the merge holds in registers.  Every output of sampled rows against the float64 oracle,
 with the bounds of the loss-head tests; every logit finite."""
 
 import numpy as np
@@ -24,6 +25,7 @@ CASES = [
     (128, 65664, 128),    # 1026
     (384, 9088, 128),     # 36 x 2 tiles, all cut: parts past both ends
     (1024, 17536, 64),    # 69 x 4 tiles: whole ones, then cut ones, on the chiplets with nine
+    (32512, 33024, 64),   # 129 x 127 tiles: up to 68 items a work group (64 looked up at once), the last cut
 ]
 
 

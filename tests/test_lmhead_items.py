@@ -1,12 +1,17 @@
 """The loss head's work items (paper_2608_00029_amd/csrc/lmhead_sched.h) cover
 every logit exactly once, for grids with and without a last partial round, and
-an item cut from a tile is at most one per work group."""
+an item cut from a tile is at most one per work group.  The built kernel holds
+the stores per tile that its waits count on."""
 
 import os
+import re
 import shutil
 import subprocess
 
 import pytest
+
+from paper_2608_00029_amd.binding import library_path
+from test_residency import _code_objects
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -52,3 +57,27 @@ def test_items_cover_every_logit_once(tmp_path):
                     "-o", exe], check=True)
     out = subprocess.run([exe], capture_output=True, text=True)
     assert out.returncode == 0 and "bad=0" in out.stdout, out.stdout
+
+
+def test_stores_per_tile(tmp_path):
+    """While a tile's stores drain, a wave waits for its oldest copies by letting
+    4 + 34 younger operations be in flight: with fewer than 34 stores in the
+    built kernel it would read a chunk that has not landed."""
+    objdump = shutil.which("llvm-objdump", path="/opt/rocm/llvm/bin:" + os.environ.get("PATH", ""))
+    if objdump is None:
+        pytest.skip("llvm-objdump not found")
+    with open(library_path(), "rb") as f:
+        blob = f.read()
+    found = 0
+    for i, elf in enumerate(_code_objects(blob)):
+        if b"lmhead_logits_stats_kernel" not in elf:
+            continue
+        path = tmp_path / f"{i}.elf"
+        path.write_bytes(elf)
+        text = subprocess.run([objdump, "-d", str(path)], capture_output=True, text=True, check=True).stdout
+        body = re.search(r"<\S*lmhead_logits_stats_kernel\S*>:\n(.*?)(\n\n|\Z)", text, re.S)[1]
+        assert len(re.findall(r"\bglobal_store_dwordx4\b", body)) == 32
+        assert len(re.findall(r"\bglobal_store_dwordx2\b", body)) == 2
+        assert not re.search(r"\b(scratch|buffer|flat)_", body)
+        found += 1
+    assert found == 1
