@@ -976,22 +976,6 @@ int cu_count() {
   return cached[dev];
 }
 
-// Work-group order of a grid of BH heads x n_tiles with per_cu work groups
-// resident per CU: `otherwise`, or kHeadGroup heads at a time where the grid
-// takes more than one round, there are at least three groups of heads and
-// sequences are short enough that a group's heads (eight per chiplet) stream
-// from its 4 MB L2.  Forward + dQ + dK/dV, over all heads / 64 at a time, us:
-// B16 H16 S512 D128 156 / 138, B16 H16 S1024 D128 432 / 401, B32 H16 S200 D128
-// 113 / 101, B32 H16 S512 D64 148 / 139, B16 H32 S1024 D64 417 / 406, B16 H16
-// S1024 D64 205 / 200; but B16 H12 S2048 D64 498 / 522 (its longest tiles then
-// start in every group's last round), B8 H16 S1024 D64 (two groups) 109 / 116,
-// and the forward of B16 H16 S512 D64 (resident at once) 19.5 / 22.4.
-constexpr int kHeadGroup = 64;
-static int work_order(int BH, int S, int n_tiles, int per_cu, int otherwise) {
-  return S <= 1024 && BH >= 3 * kHeadGroup && (int64_t)BH * n_tiles > per_cu * (int64_t)cu_count() ? -kHeadGroup
-                                                                                                   : otherwise;
-}
-
 // Ring depths per part (LDS slots of 32-row tiles): in four parts, and in two
 // at D = 128, two slots (64 KB of rings a work group, two per CU; four parts at
 // D = 128 128 KB, one).
@@ -1002,14 +986,21 @@ template <int D, int SPLIT> constexpr int bwd_nb() {
   return SPLIT == 1 ? (D == 64 ? kBwdNb64 : kBwdNb128) : D == 64 && SPLIT == 2 ? kBwdNbSplit : 2;
 }
 
+// The forward's and dQ's `order` argument, per_cu work groups resident per CU.
+template <bool CAUSAL, int SPLIT>
+static int query_order(Pass pass, int D, int BH, int S, int n_qtiles, int per_cu) {
+  const int cus = cu_count();
+  return work_order(pass, D, CAUSAL, BH, S, n_qtiles, per_cu, cus,
+                    CAUSAL ? query_band((int64_t)BH * n_qtiles, SPLIT, S, cus) : 0);
+}
+
 template <int D, bool CAUSAL, int SPLIT, int NB, bool RAG, bool STR>
 static hipError_t launch_dq_t(const BwdArgs& a, float c, int n_qtiles, hipStream_t st) {
   hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, CAUSAL, SPLIT, NB, RAG, STR>),
                      dim3((unsigned)((int64_t)a.BH * n_qtiles)), dim3(256), 0, st, (const bf16*)a.q,
                      (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.o, (const bf16*)a.dout, a.lse, (bf16*)a.dq,
                      a.ws, a.S, a.BH, n_qtiles, c, a.scale,
-                     work_order(a.BH, a.S, n_qtiles, D == 64 ? 4 : 2, CAUSAL ? query_band((int64_t)a.BH * n_qtiles, SPLIT, a.S, cu_count()) : 0),
-                     a.H,
+                     query_order<CAUSAL, SPLIT>(Pass::kDq, D, a.BH, a.S, n_qtiles, D == 64 ? 4 : 2), a.H,
                      (int)a.seq_major);
   return hipGetLastError();
 }
@@ -1035,9 +1026,7 @@ static hipError_t launch_dkdv(const BwdArgs& a, float c, hipStream_t st) {
   const int per_cu = D == 64 && SPLIT == 1 ? 3 : 2;
   const int64_t n = (int64_t)a.BH * n_ktiles, cus = cu_count();
   const int band = CAUSAL && n > cus && n <= per_cu * cus ? (int)cus : 0;
-  // (heads in groups: not without the mask at D = 128, where every work group
-  // streams the whole head: B16 H16 S512 85 us over all heads, 86-104 in groups)
-  const int order = CAUSAL || D == 64 ? work_order(a.BH, a.S, n_ktiles, per_cu, band) : band;
+  const int order = work_order(Pass::kDkdv, D, CAUSAL, a.BH, a.S, n_ktiles, per_cu, (int)cus, band);
   hipLaunchKernelGGL((attn_bwd_dkdv_bf16_kernel<D, CAUSAL, SPLIT, NB, RAG>), dim3((unsigned)((int64_t)a.BH * n_ktiles)),
                      dim3(256), 0, st, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (const bf16*)a.dout,
                      (const float*)a.ws, (bf16*)a.dk, (bf16*)a.dv, a.S, a.BH, n_ktiles, c, a.scale,
@@ -1052,8 +1041,7 @@ static hipError_t launch_fwd_split(const FwdArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, CAUSAL, SPLIT, NB, RAG>), dim3((unsigned)((int64_t)a.BH * n_qtiles)),
                      dim3(256), 0, st, (const bf16*)a.q, (const bf16*)a.k, (const bf16*)a.v, (bf16*)a.o, a.lse, a.S,
                      a.BH, n_qtiles, a.scale * kLog2e,
-                     work_order(a.BH, a.S, n_qtiles, D == 64 ? 4 : 3, CAUSAL ? query_band((int64_t)a.BH * n_qtiles, SPLIT, a.S, cu_count()) : 0),
-                     a.H,
+                     query_order<CAUSAL, SPLIT>(Pass::kFwd, D, a.BH, a.S, n_qtiles, D == 64 ? 4 : 3), a.H,
                      (int)a.seq_major);
   return hipGetLastError();
 }

@@ -1,5 +1,6 @@
 """grouped_rank (paper_2608_00029_amd/csrc/attn_sched.h) visits every (head,
-rank) once, group by group of heads and rank by rank inside a group."""
+rank) once, group by group of heads and rank by rank inside a group; work_order
+picks it on the sides of its limits (256 CUs) where it measured faster."""
 
 import os
 import shutil
@@ -32,6 +33,26 @@ int main() {
         }
         for (int s : seen) bad += s != 1;
       }
+  // pass, D, causal, heads, S, tiles, resident per CU: whether heads are grouped
+  struct { Pass pass; int D; bool causal; int BH, S, nt, per_cu; bool grouped; } rules[] = {
+      {Pass::kFwd, 128, true, 256, 1024, 8, 3, true},   {Pass::kFwd, 128, true, 191, 1024, 8, 3, false},
+      {Pass::kFwd, 128, true, 256, 1025, 9, 3, false},  {Pass::kFwd, 64, true, 256, 512, 4, 4, false},
+      {Pass::kFwd, 64, true, 257, 512, 4, 4, true},     {Pass::kFwd, 64, true, 1135, 24, 1, 4, false},
+      {Pass::kDq, 128, true, 210, 384, 3, 2, false},    {Pass::kDq, 128, true, 250, 384, 3, 2, true},
+      {Pass::kDq, 128, false, 340, 160, 2, 2, false},   {Pass::kDq, 128, false, 340, 192, 2, 2, true},
+      {Pass::kDq, 128, false, 513, 160, 2, 2, true},    {Pass::kDq, 128, false, 250, 300, 3, 2, false},
+      {Pass::kDkdv, 64, true, 340, 258, 3, 3, false},   {Pass::kDkdv, 128, true, 210, 300, 3, 2, false},
+      {Pass::kDkdv, 128, true, 210, 349, 3, 2, true},   {Pass::kDkdv, 128, true, 300, 300, 3, 2, true},
+      {Pass::kDq, 128, true, 323, 186, 2, 2, true},     {Pass::kDq, 64, false, 513, 256, 2, 4, true},
+      {Pass::kDkdv, 128, true, 323, 186, 2, 2, false},  {Pass::kDkdv, 128, true, 513, 186, 2, 2, true},
+      {Pass::kDkdv, 128, true, 323, 300, 3, 2, true},    {Pass::kDkdv, 64, true, 768, 160, 2, 3, false},
+      {Pass::kDkdv, 64, true, 942, 140, 2, 3, false},   {Pass::kDkdv, 64, false, 400, 256, 2, 3, true},
+      {Pass::kDkdv, 128, false, 400, 1024, 8, 2, false}};
+  for (auto& r : rules)
+    for (int otherwise : {0, 256})
+      if (work_order(r.pass, r.D, r.causal, r.BH, r.S, r.nt, r.per_cu, 256, otherwise) !=
+          (r.grouped ? -kHeadGroup : otherwise))
+        ++bad;
   printf("bad=%d\n", bad);
   return bad != 0;
 }
