@@ -1,8 +1,8 @@
 // bf16 attention kernels for gfx950: forward, dQ and dK/dV (section 4.2 of the
 // Nova paper), organised around memory latency and vector-ALU issue on CDNA4.
 //
-// Differences from the generic kernels (attn_fwd.hip, attn_bwd.hip, used for
-// float32):
+// (The float32 kernels, attn_fwd.hip and attn_bwd.hip, are built differently:
+// bound by their matrix instructions, they stage nothing in LDS.)
 //  * Streamed operands move in tiles of 32 rows, HBM -> LDS with
 //    global_load_lds_dwordx4 (no staging registers, no ds_write), through a
 //    ring of NB buffers.  The copy of tile t + NB - 1 is issued at the top of
@@ -16,11 +16,13 @@
 //    unrolled by the ring depth so that each LDS read names its buffer with an
 //    immediate offset: no per-iteration vector address arithmetic.
 //  * A 32-row tile is one sub-block of the matrix-core contractions.  Each
-//    wave walks its own range of sub-blocks; operands of sub-block j+1 are
-//    read from LDS (tile j+1 is always resident) while sub-block j computes.
-//  * The forward is software pipelined: iteration j runs O += P(j-1) V(j-1)
-//    and S(j+1) = K(j+1) Q^T on the matrix cores while the vector ALUs do the
-//    softmax of S(j).
+//    wave walks the sub-blocks of its part of the other axis; an operand
+//    fragment is read from LDS one contraction step before its use, or with
+//    its whole tile (fwd_lean, dkdv_lean and the kernels say which, and why).
+//  * The forward in two parts at D = 64 is software pipelined: iteration j runs
+//    O += P(j-1) V(j-1) and S(j+1) = K(j+1) Q^T on the matrix cores while the
+//    vector ALUs do the softmax of S(j).  The other forms run a block start to
+//    end and leave that overlap to the SIMD's other waves.
 //  * Only the sub-block of a wave that straddles the causal diagonal (and the
 //    ragged last one) is masked; every other sub-block is branch-free.
 #include <utility>

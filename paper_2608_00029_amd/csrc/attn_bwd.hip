@@ -223,9 +223,11 @@ static hipError_t launch_bwd_t(const BwdArgs& a, int phase, hipStream_t st) {
   const int n_tiles = (a.S + 32 * G - 1) / (32 * G);
   const int64_t n = (int64_t)a.BH * n_tiles;
   const dim3 grid((unsigned)n);
-  // dealt in alternating directions when every work group is resident from the
-  // start (dK/dV at D = 64: when at most a third of them start later, which
-  // measured 71 us against 75 at B2 H12 S1024)
+  // dealt in alternating directions in grids of few enough work groups per CU:
+  // all resident from the start, which dQ keeps three (four in the builds for
+  // whole tiles, where the limit of three was kept) of at D = 64 and two at 128,
+  // dK/dV two and one; dK/dV at D = 64 up to three, where the last third starts
+  // later (71 us against 75 at B2 H12 S1024)
   const int cus = cu_count(), dq_band = n <= (D == 64 ? 3 : 2) * cus ? cus : 0;
   const int dkdv_band = n <= (D == 64 ? 3 : 1) * cus ? cus : 0;
   if (phase != 2) {

@@ -20,9 +20,10 @@
 //    and no wave runs more than 8.
 //
 // Measured (forward + dQ + dK/dV, us; before: 128-row groups, K/V or Q/dO
-// tiles staged through LDS): B2 H12 S1024 D64 causal 378 -> 165 (floor 97 at
-// 153 TFLOP/s, what a large float32 matrix product reaches), B1 H12 S1024 D64
-// 376 -> 94, B1 H2 S128 D64 75 -> 23, B4 H16 S2048 D64 1585 -> 1420, B2 H16
+// tiles staged through LDS): B2 H12 S1024 D64 causal 378 -> 165 (at 153
+// TFLOP/s, what a large float32 matrix product reaches, 97 for the contractions
+// executed, with P and dP computed in both backward kernels, and 74 for 14 D per
+// visible pair), B1 H12 S1024 D64 376 -> 94, B1 H2 S128 D64 75 -> 23, B4 H16 S2048 D64 1585 -> 1420, B2 H16
 // S1024 D128 1062 -> 374, B1 H16 S2048 D128 not causal 1456 -> 1198.
 //
 // The contraction index of an MFMA may be permuted freely as long as both

@@ -39,9 +39,10 @@ constexpr int lmh_xcd_tile(int x, int l, int n_vt, int n_mt) {
 // complete rounds of the work groups as there are; the R < per_xcd tiles left
 // over would occupy only R of them for another whole tile's time, so each is
 // cut into f parts (the largest f of 8, 4, 2, 1 with R f <= per_xcd): halves
-// of the vocabulary first, then halves and quarters of the tokens.  A part
-// costs about 0.4 of a tile (fewer waves share a compute unit's matrix cores),
-// whatever f > 2.  1024 x 50304 x 1600 (788 tiles on 256 work groups): 197 us
+// of the vocabulary first, then halves and quarters of the tokens.  A wave
+// keeps its place in the tile, so that 8 / f of the eight waves have work, each
+// as much as in a whole tile, and all of them copy as many rows: a part costs
+// about 0.4 of a tile whatever f > 2.  1024 x 50304 x 1600 (788 tiles on 256 work groups): 197 us
 // with four rounds of whole tiles, 186 with three and a round of parts; 2944 x
 // 10496 x 704 79 / 73, 128 x 18432 x 1408 31 / 28.
 constexpr int lmh_cut(int tiles, int per_xcd) {

@@ -21,8 +21,8 @@ derived from the arithmetic):
     float64 sum of exp(z - maximum) over those logits within 1e-5 relative.
 
 Small cases compare every element; they span several 256 x 256 output tiles,
-ragged last tiles in either direction (half-width tiles whose idle waves skip
-their copies), vocabulary-tile counts that leave some chiplets without work
+ragged last tiles in either direction (half-width tiles whose idle waves only
+copy), vocabulary-tile counts that leave some chiplets without work
 and some with an extra tile, work groups of the persistent grid that walk
 several tiles, and logit scales where the per-tile maxima differ widely (so
 the merge's rescale matters).  The GPT-2 head (M 8192, N 50304, K 768) runs at

@@ -134,7 +134,7 @@ def test_workload_parity(cuda, w):
 
 # Grids large enough for the unsplit D = 64 kernels (the three-wave dK/dV among
 # them), with ragged sequence ends and without the causal mask: the small cases
-# above all take the split (two-part) kernels.
+# above take the split kernels (two or four parts), or have one or two tiles.
 UNSPLIT = [
     # B, H, S, causal
     (4, 32, 1000, True),
@@ -241,8 +241,8 @@ def test_heads_independent_of_grid(cuda):
     (1024 work groups per kernel: the dQ kernel's streamed four-wave form, the
     dK/dV grid in plain heaviest-first order) and its first six batches alone
     (768 work groups: the whole-tile dQ, the banded dK/dV order) agree bit for
-    bit.  (Grids under 768 work groups split the forward's key range, which
-    changes the summation order.)"""
+    bit.  (Smaller grids split the other axis into parts, which changes the
+    summation order.)"""
     q, k, v, do = make_inputs(8, 16, 1024, 64, "bf16", seed=2718)
     say("grid independence B8 H16 S1024 vs B6")
     full = gpu_fwd_bwd(q, k, v, do, 0.125, True)

@@ -29,7 +29,8 @@ CASES = [
     (16, 20, 60, 64, True),    # two tiles: unsplit, ragged
     (3, 40, 100, 128, False),  # four tiles, two parts, last tile of four rows
     (13, 16, 650, 64, True),   # 208 heads: three groups of 64 and one of 16, all kernels
-    (12, 16, 300, 128, False),  # 192 heads in three groups
+    (12, 16, 300, 128, False),  # 192 heads, three tiles in little more than a round: over all heads
+    (13, 16, 520, 128, True),  # 208 heads in groups at D = 128, all kernels
 ]
 
 
