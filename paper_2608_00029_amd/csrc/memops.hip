@@ -258,7 +258,7 @@ __device__ __forceinline__ void merge_stats(float& m, float& s, float m2, float 
   const float mm = fmaxf(m, m2);
   // nothing above -inf on either side: sums of 0, or NaN, and no offset to subtract
   const float off = mm == -INFINITY ? 0.f : mm;
-  s = s * exp2_hw(m - off) + s2 * exp2_hw(m2 - off);
+  s = fmaf(s2, exp2_hw(m2 - off), s * exp2_hw(m - off));
   m = mm;
 }
 
