@@ -55,6 +55,10 @@ enum class Pass { kFwd, kDq, kDkdv };
 //              Q 18.2 / 19.9, K 24.4 / 23.9, g 7: F 17.4 / 16.4, K 24.5 / 26.1; c S4096 D64, g 9: F 57.8 / 54.2,
 //              g 7: Q 59.4 / 58.2, K 82.4 / 68.7; S2048 D64, g 6: F 38.2 / 33.7, Q 45.8 / 45.8, K 61.2 / 57.7,
 //              g 7: F 40.1 / 43.3, K 64.5 / 69.3; c S256 D128, g 3: F 10.7 / 9.4, Q 13.7 / 13.6, K 16.6 / 15.0;
+//              c S222 D64, g 2.3: F 6.8 / 6.3; c S154 D64, g 2: K 8.7 / 7.6; c S147 D64, g 2.6: K 8.9 / 8.9; c S2855
+//              D64, g 6.3: Q 43.3 / 38.2; c S1659 D64, g 6.3: K 37.9 / 34.8; S261 D64, g 2.3: F 8.1 / 7.5, K 11.0 /
+//              10.1; S187 D64, g 3.5 (298 work groups of 128): F 7.9 / 7.5, K 11.1 / 10.2; S371 D64, 72 heads: K
+//              13.1 / 12.4, S377, 75 heads: 13.6 / 15.4;
 //              S256 D128, g 3: F 11.1 / 11.6, Q 14.5 / 16.1; S512 D128, g 4: F 16.7 / 16.8, Q 21.4 / 22.9,
 //              K 36.9 / 26.5; S2048 D128, g 5: F 59.1 / 61.5, K 102 / 105
 constexpr int split_parts(Pass pass, int D, bool causal, int BH, int S, int cus) {
@@ -69,20 +73,30 @@ constexpr int split_parts(Pass pass, int D, bool causal, int BH, int S, int cus)
     if (causal && nt >= 8) two = 8;
     if (nt >= 10) two = 12;
     if (causal && nt >= 32) two = nt >= 128 ? 20 : nt >= 64 ? 18 : 14;
+    if (causal && nt == 7) two = 6;
+    if (!causal && nt == 9) two = 5;
   } else if (pass == Pass::kDq) {
     if (nt >= (causal ? 16 : 32)) four = 2;
     if (causal && nt >= 12) two = 6;
     if (nt >= 16) two = 8;
-    if (causal && nt >= 20) two = nt >= 112 ? 16 : nt >= 40 ? 12 : nt >= 32 ? 10 : 9;
+    if (causal && nt >= 20) two = nt >= 40 ? 12 : nt >= 36 ? 11 : nt >= 32 ? 10 : 9;
+    if (causal && nt >= 64) two = nt >= 112 ? 16 : nt >= 88 ? 14 : 13;
   } else {
     if (nt >= (causal ? 8 : 32)) four = 2;
-    if (causal && nt >= 6) two = nt >= 12 ? 9 : nt >= 8 ? 8 : 6;
+    if (causal && nt >= 5) two = nt >= 12 ? 9 : nt >= 8 ? 8 : 6;
     if (!causal && nt >= 16) two = 8;
-    if (nt >= 24) two = causal && nt >= 64 ? 16 : 12;
+    if (nt >= 24) two = causal && nt >= 64 ? 16 : causal && nt >= 48 ? 13 : 12;
+    if (!causal && (nt == 5 || nt == 7 || nt == 9)) two = nt == 5 ? 6 : 5;
+    // (a head's work groups then share a chiplet, or two of them)
+    if (!causal && nt >= 7 && BH % 4 == 0) two = imax(two, 8);
   }
   if (D == 64 && causal && nt >= 48) four = 3;
   const long long g32 = (long long)BH * nt, g64 = (long long)BH * ((S + 63) / 64);
   if (g32 <= (long long)four * cus) return 4;
+  // (a short last tile can give an unsplit grid a second round where two parts need no third)
+  if (pass != Pass::kDq && D == 64 && !causal && nt >= 5 && (long long)BH * ((S + 127) / 128) > cus &&
+      g64 <= 2LL * cus)
+    return 2;
   // (an odd tile over: up to an eighth more 64-row groups than CUs is no loss yet)
   if (two == 4 && nt >= 8) return g32 <= 2LL * cus ? 2 : 1;
   // (a short last tile can give an unsplit grid a third round where two parts need no fifth:

@@ -35,13 +35,16 @@ MEASURED = {
     # two work groups of 32 rows per CU
     (64, False, 64, 256): (2, 2, 2), (64, True, 32, 512): (4, 4, 4), (64, False, 32, 512): (4, 2, 2),
     (64, False, 16, 1024): (4, 4, 4), (64, True, 32, 384): (4, 2, 4), (64, False, 56, 288): (2, 2, 2),
-    (64, True, 89, 224): (1, 1, 2), (64, True, 48, 384): (2, 2, 2), (64, True, 68, 450): (2, 1, 2),
+    (64, True, 89, 224): (2, 1, 2), (64, True, 84, 224): (2, 1, 2), (64, True, 105, 154): (1, 1, 2),
+    (64, True, 133, 154): (1, 1, 1), (64, False, 64, 261): (2, 1, 2), (64, False, 149, 187): (2, 1, 2),
+    (64, False, 57, 272): (2, 1, 2), (64, True, 36, 1142): (2, 2, 2), (64, False, 72, 371): (2, 1, 2), (64, False, 81, 352): (2, 1, 1), (64, True, 48, 384): (2, 2, 2), (64, True, 68, 450): (2, 1, 2),
     (64, True, 40, 777): (2, 2, 2), (64, True, 49, 650): (2, 2, 2),
     # long causal sequences: more parts, on larger grids
     (64, True, 6, 4096): (4, 4, 4), (64, True, 12, 2048): (4, 4, 4), (64, False, 12, 2048): (2, 2, 2),
     (64, True, 12, 4096): (2, 2, 2), (64, True, 24, 2048): (2, 2, 2), (64, True, 40, 1024): (2, 2, 2),
     (64, True, 14, 4096): (2, 2, 2), (64, True, 18, 4096): (2, 1, 1), (64, False, 28, 2048): (1, 1, 1),
-    (64, False, 40, 1568): (2, 1, 1),
+    (64, False, 40, 1568): (2, 1, 1), (64, True, 22, 2264): (2, 2, 2), (64, True, 18, 2855): (2, 2, 2),
+    (64, True, 31, 1659): (2, 1, 2),
     (64, True, 56, 1024): (2, 1, 1),
     # head dimension 128
     (128, True, 152, 160): (2, 1, 1),
