@@ -168,11 +168,11 @@ constexpr HeadRank grouped_rank(int bid, int BH, int ntiles, int hg) {
 }
 
 // The `order` argument of a grid of BH heads x n_tiles tiles, per_cu work
-// groups resident per CU: `otherwise` (a band or 0), or -kHeadGroup, the heads
-// taken kHeadGroup at a time, where the grid takes more than one round, there
-// are at least three groups of heads and sequences are short enough that a
-// group's heads (eight per chiplet) stream from its 4 MB L2.  Forward + dQ +
-// dK/dV, over all heads / 64 at a time, us: B16 H16 S512 D128 156 / 138, B16 H16
+// groups resident per CU: `otherwise` (a band or 0), or the heads taken up to
+// kHeadGroup at a time (the negative of their number), where the grid takes more
+// than one round, there are at least three groups of heads and sequences are
+// short enough that a group's heads (eight per chiplet) stream from its 4 MB L2.
+// Forward + dQ + dK/dV, over all heads / 64 at a time, us: B16 H16 S512 D128 156 / 138, B16 H16
 // S1024 D128 432 / 401, B32 H16 S200 D128 113 / 101, B32 H16 S512 D64 148 / 139,
 // B16 H32 S1024 D64 417 / 406, B16 H16 S1024 D64 205 / 200; but B16 H12 S2048
 // D64 498 / 522 (its longest tiles then start in every group's last round), B8
@@ -180,31 +180,37 @@ constexpr HeadRank grouped_rank(int bid, int BH, int ntiles, int hg) {
 // (resident at once) 19.5 / 22.4.  The backward keeps `otherwise`
 //  * in dK/dV without the mask at D = 128, where every work group streams the
 //    whole head: B16 H16 S512 85 over all heads, 86-104 in groups;
-//  * in up to two rounds of two or three tiles, where heavy tiles of the last
-//    group of heads would end the grid that light ones end in the order over
-//    all heads: dK/dV with the mask, two tiles (B1 H323 S186 D128 24.9 / 29.7;
-//    at D = 64 in any number of rounds: B1 H942 S140 26.6 / 28.6) or three, the last at most 48 rows, up to 1.5 rounds (B1 H210 S300 D128
-//    29.4 / 31.2, B1 H340 S258 D64 21.8 / 22.8; S349 39.1 / 38.9, B1 H300 S300
-//    49.5 / 44.6); dQ at D = 128 with the mask, three tiles, up to 1.4 rounds
-//    (B1 H210 S384 27.7 / 31.1, B1 H230 S349 30.4 / 33.0; B1 H250 S384 41.9 /
-//    40.1), and without it where the last of them has at most 48 rows (B1 H340
-//    S160 21.3 / 23.7, B1 H250 S300 37.5 / 39.4; B1 H340 S192 30.3 / 29.5).
-// (One tile per head: both orders are the same.)
+//  * in grids of little more than a round, where heavy tiles of the last group
+//    of heads would end the grid that light ones end in the order over all
+//    heads: dK/dV with the mask at D = 128 up to 1.7 rounds (B1 H202 S320 26.2 /
+//    32.5, B1 H208 S392 42.3 / 49.1; B1 H300 S384, 1.76, 53.5 / 51.1), with two
+//    tiles up to two rounds (B1 H323 S186 24.9 / 29.7), at D = 64 with two tiles
+//    in any number of rounds (B1 H942 S140 26.6 / 28.6) and with three, the last
+//    at most 48 rows, up to 1.5 (B1 H340 S258 22.8 / 23.7); dQ at D = 128 with
+//    the mask and three tiles up to 1.5 (B1 H210 S384 31.1 / 34.9, B1 H240 S264
+//    26.8 / 28.8; B1 H300 S384 43.6 / 40.9), without it and two or three tiles,
+//    the last at most 48 rows, up to two (B1 H340 S160 23.7 / 26.3, B1 H250 S300
+//    39.4 / 41.4; B1 H340 S192 29.5 / 28.7).
+// (One tile per head: both orders are the same.)  Groups are of the same size,
+// a multiple of 8 so that a head keeps its chiplet: a small last one would start
+// its heavy tiles last (dK/dV with the mask at D = 128, 64 and the rest / even:
+// B1 H208 S540 63.0 / 58.2, B1 H202 S704 80.1 / 77.6, B1 H272 S668 107.7 / 102.3).
 constexpr int kHeadGroup = 64;
 constexpr int work_order(Pass pass, int D, bool causal, int BH, int S, int n_tiles, int per_cu, int cus,
                          int otherwise) {
   const long long n = (long long)BH * n_tiles, round = (long long)per_cu * cus;
   if (n_tiles < 2 || S > 1024 || BH < 3 * kHeadGroup || n <= round) return otherwise;
-  const bool short_last = (long long)n_tiles * 128 - S >= 80;  // unsplit tiles (two or three split ones: 64 rows)
+  const bool short_last = (long long)n_tiles * 128 - S >= 80;  // (no split grid of two or three tiles gets here)
   if (pass == Pass::kDkdv) {
     if (!causal && D == 128) return otherwise;
     if (causal && n_tiles == 2 && (D == 64 || n <= 2 * round)) return otherwise;
-    if (causal && n_tiles == 3 && short_last && 2 * n <= 3 * round) return otherwise;
+    if (causal && (D == 64 ? n_tiles == 3 && short_last && 2 * n <= 3 * round : 10 * n <= 17 * round)) return otherwise;
   }
   if (pass == Pass::kDq && D == 128 && n_tiles <= 3) {
-    if (causal ? n_tiles == 3 && 5 * n <= 7 * round : short_last && n <= 2 * round) return otherwise;
+    if (causal ? n_tiles == 3 && 2 * n <= 3 * round : short_last && n <= 2 * round) return otherwise;
   }
-  return -kHeadGroup;
+  const int groups = (BH + kHeadGroup - 1) / kHeadGroup;
+  return -((BH + 8 * groups - 1) / (8 * groups) * 8);
 }
 
 // Ring with one barrier per group of G iterations (one part; G divides the
