@@ -31,9 +31,11 @@
 //  * A partial statistic covers 64 vocabulary entries, 16 lanes of four: the
 //    row maximum takes four lane rotations per token, the sums are scattered
 //    over the lanes, halving the values per exchange.
-// Whole call, transposed blocks with chunks of 64 in two slots / this: 8192 x
-// 50304 x 768 916 / 754 us, 1024 x 50304 x 1600 221 / 201, 128 x 18432 x 1408
-// 35 / 32, 1152 x 11264 x 384 30 / 27.
+// lmhead_fwd with the same inputs each pass, transposed blocks with chunks of 64
+// in two slots and whole tiles only / this: 8192 x 50304 x 768 930 / 707 us, 1024
+// x 50304 x 1600 220 / 179, 128 x 18432 x 1408 34.3 / 26.8, 1152 x 11264 x 384
+// 29.4 / 26.2; the first two with inputs that change from pass to pass 918 / 761
+// and 220 / 198.
 //
 // Partials are [M, N/64] pairs (maximum, sum of exp(z - maximum)).  Logits are
 // written as float [M, N].  Tiles are dealt to the GPU's chiplets by vocabulary

@@ -42,9 +42,9 @@ constexpr int lmh_xcd_tile(int x, int l, int n_vt, int n_mt) {
 // of the vocabulary first, then halves and quarters of the tokens.  A wave
 // keeps its place in the tile, so that 8 / f of the eight waves have work, each
 // as much as in a whole tile, and all of them copy as many rows: a part costs
-// about 0.4 of a tile whatever f > 2.  1024 x 50304 x 1600 (788 tiles on 256 work groups): 197 us
-// with four rounds of whole tiles, 186 with three and a round of parts; 2944 x
-// 10496 x 704 79 / 73, 128 x 18432 x 1408 31 / 28.
+// about 0.4 of a tile whatever f > 2.  1024 x 50304 x 1600 (788 tiles on 256 work groups): 195 us
+// with four rounds of whole tiles, 178 with three and a round of parts; 2944 x
+// 10496 x 704 75.5 / 68.2, 128 x 18432 x 1408 30.3 / 26.8.
 constexpr int lmh_cut(int tiles, int per_xcd) {
   const int rest = tiles % per_xcd;
   int f = 1;
